@@ -102,6 +102,25 @@ STT_HD Trk draw_track(const GenP &g, uint64_t j)
     return t;
 }
 
+// Bucket number of the time-extent sort for a template whose (start, end) columns fall into
+// buckets b0 and b0 + nb - 1 - e of nb per axis (e = 0 for the longest extents, b0 <= e < nb).
+// Extents form classes of cw consecutive e, numbered longest class first; within a class buckets
+// go by start, then by extent. Blocks of templates that follow each other in this order start in
+// the same columns, so the blocks that run at one time stage the same columns of the map from
+// their L2s; ordering by extent alone (cw = 1) spreads their starts over the whole map. The
+// classes keep the longest blocks first, so that the launch still ends on short ones.
+// A class of w extents from e = m on has w (m + 1) + w (w - 1) / 2 buckets: w for each start
+// b0 <= m, then one fewer for each start beyond it. Numbers run over [0, nb (nb + 1) / 2).
+STT_HD uint32_t bucket_number(uint32_t e, uint32_t b0, uint32_t cw, uint32_t nb)
+{
+    const uint32_t m = e / cw * cw, d = e - m, w = cw < nb - m ? cw : nb - m;
+    const uint32_t over = b0 > m ? b0 - m : 0u;  // starts that only extents e >= m + over reach
+    return m * (m + 1) / 2 + b0 * w - over * (over + 1) / 2 + d;
+}
+
+// Extents per class: a quarter of the axis.
+STT_HD uint32_t bucket_class(uint32_t nb) { return (nb + 3) / 4; }
+
 // ----------------------------------------------------------------------------
 // Templates with a free t_mid (Eq. 6 with its six random numbers): the time
 // coordinate is a quadratic Bezier too, with an integer t1 in [t0, t2] drawn

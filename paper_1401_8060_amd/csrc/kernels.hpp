@@ -466,11 +466,13 @@ __global__ __launch_bounds__(256) void k_argmax(const float *z, int64_t n, uint6
 
 // ---------------------------------------------------------------- binning by time extent
 // Bucket of a template: b0 = t0 >> wb, b2 = t2 >> wb (b0 <= b2), nb buckets
-// per axis. Buckets are numbered longest extent first: with e = nb - 1 -
-// (b2 - b0) (0 for the longest), bucket = e (e + 1) / 2 + b0, b0 <= e. Blocks
-// of binned templates are dispatched in that order, so the longest-running
-// blocks start first and the launch ends on short ones. Invalid given
-// templates go to bucket 0 (they are skipped when scored).
+// per axis, numbered by bucket_number: four classes of extents, longest first,
+// and by start within a class. Blocks of binned templates are dispatched in
+// that order. Blocks that run together then stage the same columns: on the
+// search map (1000 x 1000, 10^7 templates, 512 x 4 workgroups) the scorer takes
+// 1.39 ms; numbered by extent alone, 1.69 ms (classes of 20, 24, 42, 48 and 64
+// of the 126 extents: 1.59, 1.55, 1.42, 1.43, 1.46). Invalid given templates go
+// to bucket 0 (they are skipped when scored).
 //
 // The sort: count, scans, two scatters. Buckets form groups of 2^kGroupShift
 // consecutive ones. The count (one workgroup per chunk of kBinChunk templates)
@@ -554,8 +556,8 @@ __device__ __forceinline__ uint32_t bin_of(const GenP &g, const Trk *tr, const M
         draw_extent(g, first + (uint64_t)i, t0, t2);
     }
     const uint32_t b0 = (uint32_t)t0 >> wb, b2 = (uint32_t)t2 >> wb;
-    const uint32_t e = ((uint32_t)(m.T - 1) >> wb) - (b2 - b0);
-    return e * (e + 1) / 2 + b0;
+    const uint32_t nb = ((uint32_t)(m.T - 1) >> wb) + 1;
+    return bucket_number(nb - 1 - (b2 - b0), b0, bucket_class(nb), nb);
 }
 
 // The count's step for one chunk, after its histogram hist[0 .. nbins-1] is

@@ -471,6 +471,44 @@ STT_HD void ddaf_step(DdaF &s)
     s.del += s.dd;
 }
 
+// The two row forms of the LDS-DMA scorer, both kRowHi + row in 32 bits.
+// exact_row: the FMA above with kRowHi added to its integer constant (still an integer in
+// [2^52, 2^53)). One FMA, and two adds for the step.
+constexpr uint32_t kRowHi = 0x41380000u;  // high word of 1.5 * 2^20
+
+STT_HD uint32_t exact_row(double num, double invq)
+{
+    const double y = fma(num, invq, 6755399441055744.0 + 1094189056.0);  // 3 * 2^51 + kRowHi
+    uint64_t u;
+    __builtin_memcpy(&u, &y, sizeof u);
+    return (uint32_t)u;
+}
+
+// lazy_row: Y = 1.5 * 2^20 + y with y = (num + Q/2)/Q in rows, num the centred numerator: seeded
+// from the exact num by one FMA, then carried by one FMA per column with the exact difference,
+// Y += del/Q. Y lies in [2^20, 2^21), on a grid of u = 2^-32 row, and its high word is
+// 1.5 * 2^20's plus floor(y): the row, while Y's error stays below 1/(2Q) (y is at least that far
+// from an integer). After the seed and k steps the error is at most (k + 1) u/2 from rounding and,
+// from 1/Q (relative 2^-53), 2^-53 times |y| at the seed and |del|/Q at each step: at most F at the
+// seed and 2F over the steps of a quadratic inside [0, F], so 3F 2^-53 <= 3 * 2^-38 in all. With a
+// seed every R columns, R/2 u + 3 * 2^-38 < 1/(2Q) = 2^-9 / Dt^2 holds when
+// Dt^2 (32 R + 3) < 2^29: lazy_period gives the largest such R in {16, 8, 4, 2}, else 1.
+STT_HD double lazy_seed(double num, double invq) { return fma(num, invq, 1572864.5); }
+STT_HD double lazy_step(double Y, double del, double invq) { return fma(del, invq, Y); }
+STT_HD uint32_t lazy_row(double Y)
+{
+    uint64_t u;
+    __builtin_memcpy(&u, &Y, sizeof u);
+    return (uint32_t)(u >> 32);
+}
+STT_HD int lazy_period(int32_t Dt)
+{
+    const uint64_t d2 = (uint64_t)Dt * (uint64_t)Dt;
+    for (int R = 16; R > 1; R >>= 1)
+        if (d2 * (uint64_t)(32 * R + 3) < (1ull << 29)) return R;
+    return 1;
+}
+
 // ----------------------------------------------------------------------------
 // Phase factor of Eq. 8. f dtau = (fq4/16 Hz)(dtau 2^-28 s) = fq4*dtau 2^-32
 // turns, so the phase is the 32-bit wrap of fq4*dtau: exact. Per track,

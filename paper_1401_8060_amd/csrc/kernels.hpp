@@ -838,33 +838,78 @@ __global__ __launch_bounds__(kScatterWG) void k_bin_fine(int nbins, const uint32
                tsub + e0, cursor + b0, order);
 }
 
-// One LDS-DMA copy of 16 bytes per lane: lane i's 16 bytes at src land at
-// lds_dst + 16 i (lds_dst wave-uniform). Written as inline assembly so that the
-// compiler does not tie it to the LDS reads of the other slab buffer: its
-// wait-count pass cannot tell the two buffers apart and would stall each
-// wave's first read of a slab until its prefetch of the next slab had landed.
-// The caller waits for the copies itself (a full s_waitcnt and a barrier
-// before a buffer is read). A copy the compiler does not count can only make
-// its own memory waits stricter (vector memory counters drain in order).
-__device__ __forceinline__ void lds_dma_16(const float2 *src, float2 *lds_dst)
+// LDS byte address of a pointer into LDS, and the 4- or 8-byte map element at one.
+__device__ __forceinline__ uint32_t lds_addr(const void *p)
 {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float2 *)lds_dst);
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+template <typename E> __device__ __forceinline__ E lds_elem(uint32_t addr);
+template <> __device__ __forceinline__ float2 lds_elem<float2>(uint32_t addr)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));  // one 8-byte read
+    const f2 v = *(const __attribute__((address_space(3))) f2 *)(uintptr_t)addr;
+    return make_float2(v.x, v.y);
+}
+template <> __device__ __forceinline__ uint32_t lds_elem<uint32_t>(uint32_t addr)
+{
+    return *(const __attribute__((address_space(3))) uint32_t *)(uintptr_t)addr;
+}
+
+// LDS-DMA staging of columns of a folded map by a workgroup of NW waves. A wave moves 1 KB pieces
+// (16 bytes per lane): pieces w, w + NW, ... of a run of columns, which lies contiguous in the map
+// and in LDS. The copies are inline assembly so that the compiler does not tie them to the LDS
+// reads of the other slab buffer: its wait-count pass cannot tell the buffers apart and would
+// stall each wave's first read of a slab until its prefetch of the next one had landed; slab_sync
+// waits for them. Addresses stay scalar (base in SGPRs, the lane's 16 bytes as the vector offset):
+// with the 64-bit vector address and the generic LDS pointer of a plain builtin the loop around a
+// copy took 52 scalar instructions per wave and slab, and the search scorer 6-8 % more time.
+template <int NW>
+struct SlabDma {
+    const char *src;    // this wave's first piece of column 0
+    uint32_t col_bytes; // bytes per column (whole pieces)
+    uint32_t wave_off;  // 1024 * wave
+    uint32_t lane_off;  // 16 * lane
+
+    __device__ __forceinline__ SlabDma(const MapP &m, int esize)
+    {
+        wave_off = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (uint32_t)kDmaBytes;
+        const uint64_t y = (uint64_t)m.Y;  // wave-uniform, also where it was loaded through a vector register
+        const uint32_t ylo = __builtin_amdgcn_readfirstlane((uint32_t)y);
+        const uint32_t yhi = __builtin_amdgcn_readfirstlane((uint32_t)(y >> 32));
+        src = reinterpret_cast<const char *>((uint64_t)yhi << 32 | ylo) + wave_off;
+        col_bytes = __builtin_amdgcn_readfirstlane((uint32_t)m.ld * (uint32_t)esize);
+        lane_off = (threadIdx.x & 63) * 16;
+    }
+
+    // columns c0 .. c0 + ncol - 1 to LDS address dst (c0, ncol and dst wave-uniform)
+    __device__ __forceinline__ void issue(int c0, int ncol, uint32_t dst) const
+    {
+        const uint32_t bytes = (uint32_t)__builtin_amdgcn_readfirstlane(ncol) * col_bytes;
+        const char *p = src + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(c0) * col_bytes;
+        const uint32_t d = __builtin_amdgcn_readfirstlane(dst);
+        for (uint32_t o = wave_off; o < bytes; o += NW * kDmaBytes, p += NW * kDmaBytes)
+            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+                         : : "v"(lane_off), "s"(p), "s"(d + o) : "memory", "m0");
+    }
+};
+
+// Between two slabs: this wave's copies have landed and its LDS reads are done, then everyone's.
+__device__ __forceinline__ void slab_sync()
+{
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" : : : "memory");
 }
 
 // ---------------------------------------------------------------- time-slab scorer
 // One workgroup = WG lanes x TPT templates taken consecutively from the binned
 // order; wave w owns the 64*TPT consecutive entries starting at w*64*TPT, so a
 // wave's templates start and end in nearly the same columns. The workgroup
-// sweeps the union of its waves' column ranges in slabs of S columns: all lanes
-// stage a slab (F rows x S columns of p = Y/sigma, 8 B per pixel) into LDS with
-// coalesced loads, then each wave walks its own column range through the slab.
-// Every template's DDA is started at its wave's first column (rewound when the
-// template starts later), so all lanes step together: no divergent branches in
-// the inner loop, the pixels outside a template are masked by a select and
-// their LDS address clamped into the column. Per-template partial sums are FP32
-// between flush columns and FP64 across them.
+// sweeps the union of its waves' column ranges in slabs of columns staged into
+// LDS, and each wave walks its own column range through them. Every template's
+// row walk is started at its wave's first column (rewound when the template
+// starts later), so all lanes step together: no divergent branches in the inner
+// loop, the pixels outside a template are masked by a select and their LDS
+// address clamped into the column. Per-template partial sums are FP32 between
+// flush columns and FP64 across them.
 
 // Walk columns ca..cb of the current slab (column c0 at slab[0]) for the TPT
 // templates of this lane. MASK = false is the wave's core, where every
@@ -902,49 +947,262 @@ __device__ __forceinline__ void walk(int ca, int cb, int c0, const elem_t<MAPT> 
     }
 }
 
-// Walk of one aligned slab of SC columns c0 .. c0 + SC - 1 (c0 a multiple of
-// SC, SC a divisor of kFlush) at slab[0 .. SC*ldc): straight-line code, SC
-// columns x TPT templates. MASK = false when every template of the wave covers
-// every column of the slab.
-template <int SC, int TPT, bool MASK, bool HW, int SM>
-__device__ __forceinline__ void walk_slab(int c0, const elem_t<SM> *slab, int ldc, const int32_t (&t0)[TPT],
-                                          const uint32_t (&span)[TPT], const PhaseK (&pk)[TPT], DdaF (&st)[TPT],
-                                          float (&part)[TPT])
+// Row walks and sums of a lane's TPT templates in the LDS-DMA scorer. Rows are carried as
+// kRowHi + row (the low word of exact_row and the high word of lazy_row), which the LDS
+// address and the phase constant absorb: pa holds phase_a - kRowHi * phase_b (plus the rounding
+// half unit of phase_turns with the hardware cosine).
+template <int TPT>
+struct SlabTpl {
+    double num[TPT], del[TPT], dd[TPT], invq[TPT], Y[TPT];
+    uint32_t pa[TPT], pb[TPT];
+    uint32_t ext[TPT];  // first column | (columns - 1) << 16; kNoExtent: no template, never active
+    float part[TPT];
+};
+constexpr uint32_t kNoExtent = 0xFFFFu;
+
+// part + the Eq. 8 term (add_term_pol) of a pixel at kRowHi + row = r, pa as in SlabTpl.
+template <bool HW, typename E>
+__device__ __forceinline__ float add_term_hi(float part, uint32_t pa, uint32_t pb, uint32_t r, E v)
 {
-#pragma unroll
-    for (int j = 0; j < SC; ++j) {
-        const elem_t<SM> *col = slab + j * ldc;
+    const uint32_t ph = r * pb + pa + pol_arg(v);
+    if constexpr (HW) {
+        const float x = __builtin_bit_cast(float, __builtin_amdgcn_alignbit(0x7Fu, ph, 9u));
+        return fmaf(__builtin_amdgcn_cosf(x), pol_mag(v), part);
+    } else {
+        return part + rot_re(ph, pol_mag(v), 0.0f);
+    }
+}
+
+enum : int { kWalkMask = 0, kWalkExact = 1, kWalkLazy = 2 };
+
+// Walk of one aligned slab of SC columns c0 .. c0 + SC - 1 at LDS address base (col_bytes per
+// column): straight-line code, SC columns x TPT templates.
+//   kWalkMask   some template of the wave does not cover every column: exact rows, selects
+//   kWalkExact  the wave's core, exact rows
+//   kWalkLazy   the wave's core, rows from the lazily seeded Y (one FP64 operation fewer per pixel)
+// A column's rows and LDS reads are issued before the previous column's terms are evaluated (the
+// scheduling barriers keep that order), so a gather has a column's worth of work to land behind:
+// 1.17 -> 1.12 ms on the search map with 1024 x 2, 1.17 -> 1.15 with 512 x 4.
+template <int SC, int TPT, bool HW, typename E, int KIND>
+__device__ __forceinline__ void walk_slab(uint32_t c0, uint32_t base, uint32_t col_bytes, SlabTpl<TPT> &s)
+{
+    constexpr uint32_t kShift = sizeof(E) == 8 ? 3 : 2;
+    uint32_t r[2][TPT];
+    E v[2][TPT];
+    bool act[2][TPT];
+    auto fetch = [&](int j) {
+        const int b = j & 1;
+        const uint32_t col = base + (uint32_t)j * col_bytes - (kRowHi << kShift);
+        uint32_t c = c0 + (uint32_t)j;
+        if constexpr (KIND == kWalkMask) asm("" : "+s"(c));  // else j - t0 of every column is kept in registers
 #pragma unroll
         for (int q = 0; q < TPT; ++q) {
-            const int32_t row = ddaf_row(st[q]);
-            if (MASK) {
-                const bool act = (uint32_t)(c0 + j) - (uint32_t)t0[q] <= span[q];
-                const float v = add_term_m<HW, SM>(part[q], pk[q], row, col[act ? row : 0]);
-                part[q] = act ? v : part[q];
-            } else {
-                part[q] = add_term_m<HW, SM>(part[q], pk[q], row, col[row]);
+            r[b][q] = KIND == kWalkLazy ? lazy_row(s.Y[q]) : exact_row(s.num[q], s.invq[q]);
+            if constexpr (KIND == kWalkMask) {
+                act[b][q] = c - (s.ext[q] & 0xFFFFu) <= s.ext[q] >> 16;
+                r[b][q] = act[b][q] ? r[b][q] : kRowHi;
             }
-            ddaf_step(st[q]);
+            v[b][q] = lds_elem<E>((r[b][q] << kShift) + col);
+            if constexpr (KIND == kWalkLazy) s.Y[q] = lazy_step(s.Y[q], s.del[q], s.invq[q]);
+            else s.num[q] += s.del[q];
+            s.del[q] += s.dd[q];
         }
+    };
+    fetch(0);
+#pragma unroll
+    for (int j = 0; j < SC; ++j) {
+        if (j + 1 < SC) fetch(j + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < TPT; ++q) {
+            const float p = add_term_hi<HW>(s.part[q], s.pa[q], s.pb[q], r[j & 1][q], v[j & 1][q]);
+            s.part[q] = KIND != kWalkMask || act[j & 1][q] ? p : s.part[q];
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
+    // the sums are used here: without this the compiler moves the slab's terms into the block that
+    // reads them next, with every gathered element spilled on the way
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) asm volatile("" : "+v"(s.part[q]));
+}
+
+// The block's best key from its lanes' keys: waves by shuffles, then across waves through LDS.
+template <int WG>
+__device__ __forceinline__ uint64_t block_best(uint64_t key, uint64_t *kred)
+{
+    key = wave_max_u64(key);
+    if ((threadIdx.x & 63) == 0) kred[threadIdx.x >> 6] = key;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < WG / 64; ++w) key = kred[w] > key ? kred[w] : key;
+    return key;  // valid in thread 0
 }
 
 // One block of WG*TPT consecutive entries of `order` (block index b): the
 // whole slab sweep for those templates. slab is the dynamic LDS, bnd two LDS
 // ints. Callable repeatedly by a persistent workgroup. Templates are drawn
-// (tr == NULL) or read from tr and validated.
-// SC > 0: a folded map (kMapPol: 8 bytes per pixel, kMapPolH: 4 bytes; columns
-// padded to whole 1 KB pieces) is staged with LDS DMA into two slab buffers of
-// SC columns (double buffering: slab k+1 streams in while slab k is walked).
-// Slabs are aligned to multiples of SC on the absolute column grid, so the FP32
-// partial sums are flushed between slabs and a slab is one straight-line
-// walk_slab; each wave starts its rows at its first aligned column (columns
-// before a template's start and after its end are masked, so the extra columns
-// change nothing). SC = 0: the lanes stage S columns through registers into one
-// buffer (unfolded formats are converted to Cartesian p on the way; a folded
-// map is copied as it is) and walk them column by column.
+// (tr == NULL) or read from tr and validated. The folded map (kMapPol: 8 bytes
+// per pixel, kMapPolH: 4 bytes; columns padded to whole 1 KB pieces) is staged
+// with LDS DMA into two slab buffers of SC columns (double buffering: slab k+1
+// streams in while slab k is walked). Slabs are aligned to multiples of SC on the
+// absolute column grid, so the FP32 partial sums are flushed between slabs and
+// a slab is one straight-line walk_slab; each wave starts its rows at its first
+// aligned column (columns before a template's start and after its end are
+// masked, so the extra columns change nothing). A wave passes its slabs in
+// phases, each a loop of its own so that no state is copied between branches:
+// waiting for its first column, masked, core, masked, waiting for the others.
+// What bounds it: vector-ALU issue (0.82 ms of the search map's 1.12 with neither LDS reads,
+// staging nor barriers), then the random 8-byte LDS gathers (7 clocks each) and the staging.
 template <int WG, int TPT, bool HW, int MAPT, int SC>
 __device__ __forceinline__ uint64_t score_block(const MapP &m, const GenP &g, const Trk *tr, const uint32_t *order,
+                                                uint64_t first, int64_t n, int64_t b, int32_t norm, float *snr,
+                                                float2 *slab_raw, int *bnd, uint64_t *kred)
+{
+    static_assert(kFlush % SC == 0, "slabs must tile the flush grid");
+    using E = elem_t<MAPT>;
+    __syncthreads();  // LDS of a previous block is no longer read
+    if (threadIdx.x == 0) { bnd[0] = 0x7fffffff; bnd[1] = -1; }
+
+    const int lane = threadIdx.x & 63;
+    const int64_t wbase = b * (WG * TPT) + (int64_t)(threadIdx.x >> 6) * (64 * TPT) + lane;
+    const bool expl = tr != nullptr;
+    SlabTpl<TPT> s;
+    double acc[TPT];
+    Trk tk[TPT];
+    int lo = 0x7fffffff, hi = -1;        // union of this wave's templates
+    int clo = -1, chi = 0x7fffffff;      // intersection (the core)
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) {
+        const int64_t e = wbase + q * 64;
+        const bool live = e < n;
+        const uint32_t idx = live ? order[e] : 0u;
+        Trk t = expl ? tr[idx] : draw_track(g, first + idx);
+        const bool ok = live && (!expl || track_ok(t, m));
+        if (!ok) t = Trk{0, 1, 0u, 0u, 0u, 0};
+        tk[q] = t;
+        s.ext[q] = ok ? (uint32_t)t.t0 | (uint32_t)(t.t2 - t.t0) << 16 : kNoExtent;
+        const PhaseK pk = phase_k(m, t.dtau);
+        s.pb[q] = pk.pb;
+        s.pa[q] = pk.pa - kRowHi * pk.pb + (HW ? 256u : 0u);
+        s.part[q] = 0.0f;
+        acc[q] = 0.0;
+        if (ok) {
+            lo = min(lo, t.t0);
+            hi = max(hi, t.t2);
+            clo = max(clo, t.t0);
+            chi = min(chi, t.t2);
+        } else {
+            clo = 0x7fffffff;  // a lane without a template: no unmasked core for this wave
+            chi = -1;
+        }
+    }
+    int dmax = 0;  // longest template
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) dmax = max(dmax, (int)(s.ext[q] >> 16));
+    lo = wave_min_i32(lo);
+    hi = wave_max_i32(hi);
+    clo = wave_max_i32(clo);
+    chi = wave_min_i32(chi);
+    const int seed_cols = lazy_period(wave_max_i32(dmax));
+    // the rows start at the wave's first column, aligned down to a slab boundary
+    const int start = lo == 0x7fffffff ? 0 : lo & ~(SC - 1);
+    // core slabs lie in [core0, core1)
+    int core0 = hi + 1, core1 = hi + 1;
+    if (clo <= chi) {
+        const int a0 = (clo + SC - 1) & ~(SC - 1), a1 = (chi + 1) & ~(SC - 1);
+        if (a0 < a1) { core0 = a0; core1 = a1; }
+    }
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) {
+        const DdaF d = ddaf_init_at(tk[q], start - tk[q].t0);
+        s.num[q] = d.num;
+        s.del[q] = d.del;
+        s.dd[q] = d.dd;
+        s.invq[q] = d.invq;
+    }
+    __syncthreads();
+    if (lane == 0) {
+        atomicMin(&bnd[0], lo);
+        atomicMax(&bnd[1], hi);
+    }
+    __syncthreads();
+    const int c_first = __builtin_amdgcn_readfirstlane(bnd[0]), c_last = __builtin_amdgcn_readfirstlane(bnd[1]);
+    const SlabDma<WG / 64> dma(m, (int)sizeof(E));
+    const uint32_t col_bytes = dma.col_bytes, buf0 = lds_addr(slab_raw), buf1 = buf0 + SC * col_bytes;
+    int c0 = c_first & ~(SC - 1);
+    if (c_first <= c_last) dma.issue(c0, min(SC, c_last - c0 + 1), buf0);
+    uint32_t cur = buf1;
+    // slab c0: its copies have landed, the next one's are on their way; returns its LDS address
+    auto next_slab = [&](int c) {
+        slab_sync();
+        const uint32_t other = cur;
+        cur = buf0 + buf1 - cur;
+        if (c + SC <= c_last) dma.issue(c + SC, min(SC, c_last - c - SC + 1), other);
+        return cur;
+    };
+    auto flush = [&](int c) {
+        if (((c + SC) & (kFlush - 1)) == 0) {  // wave-uniform: the slab ends a flush group
+#pragma unroll
+            for (int q = 0; q < TPT; ++q) {
+                acc[q] += s.part[q];
+                s.part[q] = 0.0f;
+            }
+        }
+    };
+    for (; c0 < start && c0 <= c_last; c0 += SC) next_slab(c0);
+    for (; c0 < core0 && c0 <= hi; c0 += SC) {
+        walk_slab<SC, TPT, HW, E, kWalkMask>(c0, next_slab(c0), col_bytes, s);
+        flush(c0);
+    }
+    if (seed_cols >= SC) {
+        int seeded = c0;  // the column of num
+        auto seed = [&](int c) {
+            const double d = (double)(c - seeded), e = -0.5 * d * (d + 1.0);
+#pragma unroll
+            for (int q = 0; q < TPT; ++q) {
+                s.num[q] = fma(e, s.dd[q], fma(d, s.del[q], s.num[q]));
+                s.Y[q] = lazy_seed(s.num[q], s.invq[q]);
+            }
+            seeded = c;
+        };
+        if (c0 < core1) seed(c0);
+        for (; c0 < core1; c0 += SC) {
+            walk_slab<SC, TPT, HW, E, kWalkLazy>(c0, next_slab(c0), col_bytes, s);
+            flush(c0);
+            if (((c0 + SC) & (seed_cols - 1)) == 0) seed(c0 + SC);
+        }
+        if (seeded != c0) seed(c0);
+    } else {
+        for (; c0 < core1; c0 += SC) {
+            walk_slab<SC, TPT, HW, E, kWalkExact>(c0, next_slab(c0), col_bytes, s);
+            flush(c0);
+        }
+    }
+    for (; c0 <= hi; c0 += SC) {
+        walk_slab<SC, TPT, HW, E, kWalkMask>(c0, next_slab(c0), col_bytes, s);
+        flush(c0);
+    }
+    for (; c0 <= c_last; c0 += SC) next_slab(c0);
+
+    uint64_t key = 0;
+#pragma unroll
+    for (int q = 0; q < TPT; ++q) {
+        const int64_t e = wbase + q * 64;
+        if (e >= n) continue;
+        const uint32_t idx = order[e];
+        const float z = s.ext[q] != kNoExtent ? finish(acc[q] + s.part[q], (int32_t)(s.ext[q] >> 16) + 1, norm, m.scale)
+                                        : __builtin_nanf("");
+        if (snr) snr[idx] = z;
+        const uint64_t k = key_encode(z, (uint32_t)(first + idx));
+        key = k > key ? k : key;
+    }
+    return block_best<WG>(key, kred);
+}
+
+// The same for maps whose columns do not fit two DMA slabs (or with DMA staging off): the lanes
+// stage S columns through registers into one buffer and walk them column by column.
+template <int WG, int TPT, bool HW, int MAPT>
+__device__ __forceinline__ uint64_t score_block_regs(const MapP &m, const GenP &g, const Trk *tr, const uint32_t *order,
                                                 uint64_t first, int64_t n, int64_t b, int S, int32_t norm, float *snr,
                                                 float2 *slab_raw, int *bnd, uint64_t *kred)
 {
@@ -997,8 +1255,7 @@ __device__ __forceinline__ uint64_t score_block(const MapP &m, const GenP &g, co
     DdaF st[TPT];
     float part[TPT];
     double acc[TPT];
-    // the rows start at the wave's first column (aligned down to a slab boundary when slabs are)
-    const int start = lo == 0x7fffffff ? 0 : (SC > 0 ? lo & ~(SC - 1) : lo);
+    const int start = lo == 0x7fffffff ? 0 : lo;  // the rows start at the wave's first column
 #pragma unroll
     for (int q = 0; q < TPT; ++q) {
         st[q] = ddaf_init_at(tk[q], start - tk[q].t0);
@@ -1014,69 +1271,29 @@ __device__ __forceinline__ uint64_t score_block(const MapP &m, const GenP &g, co
     const int c_first = __builtin_amdgcn_readfirstlane(bnd[0]), c_last = __builtin_amdgcn_readfirstlane(bnd[1]);
     const int F = m.F;
 
-    if constexpr (SC > 0) {
-        static_assert(kFlush % SC == 0, "slabs must tile the flush grid");
-        // m.ld is a whole number of 1 KB pieces and the columns are contiguous, so
-        // the slab of columns c0.. is one run of pieces, piece ch at byte offset
-        // 1024 ch in the map and in the buffer (counted below in 8-byte units).
-        const int ldc = (int)m.ld;
-        const int col8 = ldc * (int)sizeof(E) / 8, per_col = col8 / (kDmaBytes / 8);
-        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        auto issue = [&](int c0, int bsel) {
-            const int nchunk = min(SC, c_last - c0 + 1) * per_col;
-            const float2 *src = m.Y + (int64_t)c0 * col8 + lane * 2;
-            float2 *dst = slab_raw + (size_t)bsel * SC * col8;
-            for (int ch = wave; ch < nchunk; ch += WG / 64)
-                lds_dma_16(src + ch * (kDmaBytes / 8), dst + ch * (kDmaBytes / 8));
-        };
-        const int a_first = c_first & ~(SC - 1);
-        // this wave's slabs: from its aligned first column to its last; the core slabs lie in [clo, chi]
-        const int w_lo = start, w_hi = hi;
-        if (c_first <= c_last) issue(a_first, 0);
-        int k = 0;
-        for (int c0 = a_first; c0 <= c_last; c0 += SC, ++k) {
-            __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of slab k have landed
-            __syncthreads();                // so have everyone's, and slab k-1 is no longer read
-            if (c0 + SC <= c_last) issue(c0 + SC, (k + 1) & 1);
-            if (c0 < w_lo || c0 > w_hi) continue;  // wave-uniform
-            const E *cur = reinterpret_cast<const E *>(slab_raw + (size_t)(k & 1) * SC * col8);
-            if (c0 >= clo && c0 + SC - 1 <= chi)
-                walk_slab<SC, TPT, false, HW, SM>(c0, cur, ldc, t0, span, pk, st, part);
-            else
-                walk_slab<SC, TPT, true, HW, SM>(c0, cur, ldc, t0, span, pk, st, part);
-            if (((c0 + SC) & (kFlush - 1)) == 0) {  // wave-uniform: the slab ends a flush group
-#pragma unroll
-                for (int q = 0; q < TPT; ++q) {
-                    acc[q] += part[q];
-                    part[q] = 0.0f;
-                }
-            }
-        }
-    } else {
-        E *slab = reinterpret_cast<E *>(slab_raw);
-        // staging walk: element e = tid + i*WG of the slab is (column e / F, row e % F)
-        const int dcol = WG / F, drow = WG % F;
-        const int col0 = threadIdx.x / F, row0 = threadIdx.x % F;
-        for (int c0 = c_first; c0 <= c_last; c0 += S) {
-            const int ncol = min(S, c_last - c0 + 1);
-            __syncthreads();  // the previous slab has been consumed
-            {
-                int col = col0, r = row0;
-                const int64_t base = (int64_t)c0 * m.ld;
+    E *slab = reinterpret_cast<E *>(slab_raw);
+    // staging walk: element e = tid + i*WG of the slab is (column e / F, row e % F)
+    const int dcol = WG / F, drow = WG % F;
+    const int col0 = threadIdx.x / F, row0 = threadIdx.x % F;
+    for (int c0 = c_first; c0 <= c_last; c0 += S) {
+        const int ncol = min(S, c_last - c0 + 1);
+        __syncthreads();  // the previous slab has been consumed
+        {
+            int col = col0, r = row0;
+            const int64_t base = (int64_t)c0 * m.ld;
 #pragma unroll 4
-                for (int e = threadIdx.x; e < ncol * F; e += WG) {
-                    slab[col * F + r] = load_e<MAPT>(m, base + (int64_t)col * m.ld + r);
-                    r += drow;
-                    col += dcol;
-                    if (r >= F) { r -= F; ++col; }
-                }
+            for (int e = threadIdx.x; e < ncol * F; e += WG) {
+                slab[col * F + r] = load_e<MAPT>(m, base + (int64_t)col * m.ld + r);
+                r += drow;
+                col += dcol;
+                if (r >= F) { r -= F; ++col; }
             }
-            __syncthreads();
-            const int ca = max(c0, lo), cb = min(c0 + ncol - 1, hi);  // this wave's columns in the slab
-            walk<TPT, true, HW, SM>(ca, min(cb, clo - 1), c0, slab, F, t0, span, pk, st, part, acc);
-            walk<TPT, false, HW, SM>(max(ca, clo), min(cb, chi), c0, slab, F, t0, span, pk, st, part, acc);
-            walk<TPT, true, HW, SM>(max(ca, chi + 1), cb, c0, slab, F, t0, span, pk, st, part, acc);
         }
+        __syncthreads();
+        const int ca = max(c0, lo), cb = min(c0 + ncol - 1, hi);  // this wave's columns in the slab
+        walk<TPT, true, HW, SM>(ca, min(cb, clo - 1), c0, slab, F, t0, span, pk, st, part, acc);
+        walk<TPT, false, HW, SM>(max(ca, clo), min(cb, chi), c0, slab, F, t0, span, pk, st, part, acc);
+        walk<TPT, true, HW, SM>(max(ca, chi + 1), cb, c0, slab, F, t0, span, pk, st, part, acc);
     }
 
     uint64_t key = 0;
@@ -1088,24 +1305,30 @@ __device__ __forceinline__ uint64_t score_block(const MapP &m, const GenP &g, co
         const uint64_t k = key_encode(z, (uint32_t)(first + idx[q]));
         key = k > key ? k : key;
     }
-    // the block's best key: waves by shuffles, then across waves through LDS
-    key = wave_max_u64(key);
-    if (lane == 0) kred[threadIdx.x >> 6] = key;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        for (int w = 1; w < WG / 64; ++w) key = kred[w] > key ? kred[w] : key;
-    return key;  // valid in thread 0
+    return block_best<WG>(key, kred);
 }
 
 // One block of binned templates per workgroup. Each workgroup stores its best
 // key in its own slot of wg_keys (no atomics: many same-address atomics from
 // every wave serialise across the chip); k_reduce_keys folds the slots.
-// At least 4 waves per SIMD (at most 128 VGPRs), so that two workgroups of 512 lanes, or four of
-// 256, can share a CU when their slabs fit its LDS.
-constexpr int kSlabWavesPerSimd = 4;
+// Four templates per lane: at least 4 waves per SIMD (at most 128 VGPRs), so that two workgroups
+// of 512 lanes, or four of 256, can share a CU when their slabs fit its LDS. Two per lane with DMA
+// staging: 8 waves (64 VGPRs, two workgroups of 1024 lanes).
+template <int TPT, int SC> constexpr int kSlabWavesPerSimd = TPT <= 2 && SC > 0 ? 8 : 4;
 
 template <int WG, int TPT, bool HW, int MAPT, int SC>
-__global__ __launch_bounds__(WG, kSlabWavesPerSimd) void k_score_slab(MapP m, GenP g, const Trk *tr,
+__device__ __forceinline__ uint64_t score_block_any(const MapP &m, const GenP &g, const Trk *tr, const uint32_t *order,
+                                                    uint64_t first, int64_t n, int64_t b, int S, int32_t norm,
+                                                    float *snr, float2 *slab, int *bnd, uint64_t *kred)
+{
+    if constexpr (SC > 0)
+        return score_block<WG, TPT, HW, MAPT, SC>(m, g, tr, order, first, n, b, norm, snr, slab, bnd, kred);
+    else
+        return score_block_regs<WG, TPT, HW, MAPT>(m, g, tr, order, first, n, b, S, norm, snr, slab, bnd, kred);
+}
+
+template <int WG, int TPT, bool HW, int MAPT, int SC>
+__global__ __launch_bounds__(WG, (kSlabWavesPerSimd<TPT, SC>)) void k_score_slab(MapP m, GenP g, const Trk *tr,
                                                                       const uint32_t *order, uint64_t first,
                                                                       int64_t n, int S, int32_t norm, float *snr,
                                                                       uint64_t *wg_keys)
@@ -1113,8 +1336,8 @@ __global__ __launch_bounds__(WG, kSlabWavesPerSimd) void k_score_slab(MapP m, Ge
     extern __shared__ float2 slab[];
     __shared__ int bnd[2];
     __shared__ uint64_t kred[WG / 64];
-    const uint64_t key = score_block<WG, TPT, HW, MAPT, SC>(m, g, tr, order, first, n, (int64_t)blockIdx.x, S, norm,
-                                                            snr, slab, bnd, kred);
+    const uint64_t key = score_block_any<WG, TPT, HW, MAPT, SC>(m, g, tr, order, first, n, (int64_t)blockIdx.x, S,
+                                                                norm, snr, slab, bnd, kred);
     if (threadIdx.x == 0) wg_keys[blockIdx.x] = key;
 }
 
@@ -1331,22 +1554,14 @@ __global__ __launch_bounds__(WG, TPT == 1 ? 8 : 1) void k_score_tm_slab(MapP m, 
     const int c_first = __builtin_amdgcn_readfirstlane(bnd[0]), c_last = __builtin_amdgcn_readfirstlane(bnd[1]);
     using E = elem_t<MAPT>;
     const int ldc = (int)m.ld;
-    const int col8 = ldc * (int)sizeof(E) / 8, per_col = col8 / (kDmaBytes / 8);  // 8-byte units per column
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    auto issue = [&](int c0, int bsel) {
-        const int nchunk = min(S, c_last - c0 + 1) * per_col;
-        const float2 *src = m.Y + (int64_t)c0 * col8 + lane * 2;
-        float2 *dst = slab + (size_t)bsel * S * col8;
-        for (int ch = wave; ch < nchunk; ch += WG / 64)
-            lds_dma_16(src + ch * (kDmaBytes / 8), dst + ch * (kDmaBytes / 8));
-    };
-    if (c_first <= c_last) issue(c_first, 0);
+    const SlabDma<WG / 64> dma(m, (int)sizeof(E));
+    const uint32_t buf0 = lds_addr(slab), slab_bytes = (uint32_t)S * dma.col_bytes;
+    if (c_first <= c_last) dma.issue(c_first, min(S, c_last - c_first + 1), buf0);
     int kk = 0;
     for (int c0 = c_first; c0 <= c_last; c0 += S, ++kk) {
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of slab kk have landed
-        __syncthreads();                // so have everyone's, and slab kk-1 is no longer read
-        if (c0 + S <= c_last) issue(c0 + S, (kk + 1) & 1);
-        const E *cur = reinterpret_cast<const E *>(slab + (size_t)(kk & 1) * S * col8);
+        slab_sync();  // slab kk has landed and slab kk-1 is no longer read
+        if (c0 + S <= c_last) dma.issue(c0 + S, min(S, c_last - c0 - S + 1), buf0 + ((kk + 1) & 1) * slab_bytes);
+        const E *cur = reinterpret_cast<const E *>(reinterpret_cast<const char *>(slab) + (size_t)(kk & 1) * slab_bytes);
         const int ncol = min(S, c_last - c0 + 1);
         const int ca = max(c0, lo), cb = min(c0 + ncol - 1, hi);
         walk_tm<TPT, true, HW>(ca, min(cb, clo - 1), c0, cur, ldc, t0, span, rk, pk, Dc, dt2c, part, acc);
@@ -1603,22 +1818,14 @@ __global__ __launch_bounds__(WG) void k_score_md_slab(MapP m, GenP g, const Trk 
     const int c_first = __builtin_amdgcn_readfirstlane(bnd[0]), c_last = __builtin_amdgcn_readfirstlane(bnd[1]);
     using E = elem_t<MAPT>;
     const int ldc = (int)m.ld;
-    const int col8 = ldc * (int)sizeof(E) / 8, per_col = col8 / (kDmaBytes / 8);  // 8-byte units per column
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    auto issue = [&](int c0, int bsel) {
-        const int nchunk = min(S, c_last - c0 + 1) * per_col;
-        const float2 *src = m.Y + (int64_t)c0 * col8 + lane * 2;
-        float2 *dst = slab + (size_t)bsel * S * col8;
-        for (int ch = wave; ch < nchunk; ch += WG / 64)
-            lds_dma_16(src + ch * (kDmaBytes / 8), dst + ch * (kDmaBytes / 8));
-    };
-    if (c_first <= c_last) issue(c_first, 0);
+    const SlabDma<WG / 64> dma(m, (int)sizeof(E));
+    const uint32_t buf0 = lds_addr(slab), slab_bytes = (uint32_t)S * dma.col_bytes;
+    if (c_first <= c_last) dma.issue(c_first, min(S, c_last - c_first + 1), buf0);
     int kk = 0;
     for (int c0 = c_first; c0 <= c_last; c0 += S, ++kk) {
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of slab kk have landed
-        __syncthreads();                // so have everyone's, and slab kk-1 is no longer read
-        if (c0 + S <= c_last) issue(c0 + S, (kk + 1) & 1);
-        const E *cur = reinterpret_cast<const E *>(slab + (size_t)(kk & 1) * S * col8);
+        slab_sync();  // slab kk has landed and slab kk-1 is no longer read
+        if (c0 + S <= c_last) dma.issue(c0 + S, min(S, c_last - c0 - S + 1), buf0 + ((kk + 1) & 1) * slab_bytes);
+        const E *cur = reinterpret_cast<const E *>(reinterpret_cast<const char *>(slab) + (size_t)(kk & 1) * slab_bytes);
         const int ncol = min(S, c_last - c0 + 1);
         const int ca = max(c0, lo), cb = min(c0 + ncol - 1, hi);
         walk_md<TPT, true, HW>(ca, min(cb, clo - 1), c0, cur, ldc, t0, span, dg, st, part, acc);
@@ -1747,8 +1954,23 @@ __global__ __launch_bounds__(kScatterWG) void k_bin_fine_batch(const BatchMap *m
                tsub + e0, cursor + d.bin0 + b0, order);
 }
 
+// A record read by every lane at one address, kept in scalar registers (its plain loads would hold
+// it in vector registers, which the scorer needs).
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T *p)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[sizeof(T) / 4];
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(p);
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readfirstlane(src[i]);
+    T v;
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
 template <int WG, int TPT, bool HW, int MAPT, int SC>
-__global__ __launch_bounds__(WG, kSlabWavesPerSimd) void k_score_batch(const BatchMap *maps, int n_maps,
+__global__ __launch_bounds__(WG, (kSlabWavesPerSimd<TPT, SC>)) void k_score_batch(const BatchMap *maps, int n_maps,
                                                                        const uint32_t *item_start, uint32_t *queue,
                                                                        const uint32_t *order, int32_t norm,
                                                                        uint64_t *best)
@@ -1762,12 +1984,12 @@ __global__ __launch_bounds__(WG, kSlabWavesPerSimd) void k_score_batch(const Bat
         __syncthreads();
         if (threadIdx.x == 0) item_s = atomicAdd(queue, 1u);
         __syncthreads();
-        const uint32_t item = item_s;
+        const uint32_t item = __builtin_amdgcn_readfirstlane(item_s);
         if (item >= total) break;  // every workgroup reaches this: the queue only grows
-        const int mi = find_slot(item_start, n_maps, item);
-        const BatchMap d = maps[mi];
-        const uint64_t key = score_block<WG, TPT, HW, MAPT, SC>(d.m, d.g, nullptr, order + d.order0, 0, d.n,
-                                                                   (int64_t)(item - item_start[mi]), d.S, norm,
+        const int mi = __builtin_amdgcn_readfirstlane(find_slot(item_start, n_maps, item));
+        const BatchMap d = load_uniform(maps + mi);
+        const uint64_t key = score_block_any<WG, TPT, HW, MAPT, SC>(d.m, d.g, nullptr, order + d.order0, 0, d.n,
+                                                                   (int64_t)(item - __builtin_amdgcn_readfirstlane(item_start[mi])), d.S, norm,
                                                                    d.snr, slab, bnd, kred);
         // one atomic per item, spread over the maps' keys
         if (threadIdx.x == 0 && key) atomicMax((unsigned long long *)(best + mi), (unsigned long long)key);

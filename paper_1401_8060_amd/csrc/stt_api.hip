@@ -803,6 +803,65 @@ stt_status check_spectro(stt_ctx *c, const stt_spectro *p)
 // 2 / Nrm with Nrm = M dt 3/8 (the Hann window's mean square)
 float cross_scale(const stt_spectro *p) { return (float)(2.0 / ((double)p->M / p->fs * 0.375)); }
 
+// The K best of src's n elements (stt_topk's launches), or with last_only the K-th best score alone.
+template <typename SRC>
+stt_status topk_launch(stt_ctx *c, SRC src, int64_t n, int64_t first, int32_t K, int last_only, int64_t *idx_dev,
+                       float *val_dev)
+{
+    const size_t st_bytes = (sizeof(TopkState) + 255) & ~(size_t)255;
+    const stt_status s = ensure_aux(c, st_bytes + sizeof(uint64_t) * (size_t)kTopkCand);
+    if (s != STT_OK) return s;
+    TopkState *st = (TopkState *)c->aux;
+    uint64_t *cand = (uint64_t *)((char *)c->aux + st_bytes);
+    // 8 elements per lane where that still fills the chip; each workgroup flushes a histogram
+    const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 2047) / 2048, 1024));
+    hipLaunchKernelGGL(k_topk_init, dim3(kTopkPasses * kTopkBins / 1024), dim3(1024), 0, c->stream, st, (uint32_t)K);
+    for (int pass = 0; pass < kTopkPasses; ++pass)
+        hipLaunchKernelGGL(k_topk_hist<SRC>, dim3(grid), dim3(256), 0, c->stream, src, n, (uint64_t)first, st, pass);
+    hipLaunchKernelGGL(k_topk_gather<SRC>, dim3(grid), dim3(256), 0, c->stream, src, n, (uint64_t)first, st, cand);
+    const unsigned rgrid = (unsigned)((std::min<int64_t>(n, kTopkCand) + 63) / 64);
+    hipLaunchKernelGGL(k_topk_rank, dim3(rgrid), dim3(256), 0, c->stream, (const TopkState *)st, (const uint64_t *)cand, K,
+                       last_only, idx_dev, val_dev);
+    STT_HIP(c, hipGetLastError());
+    return STT_OK;
+}
+
+// Counts (and FAP = count / n_ref) of n_q query keys against n_ref reference keys: directly up to
+// kLouderDirect references, else by ranks in passes of kRankTiles tiles of queries. The ranks need
+// scratch; a call that cannot have it (no memory, or not yet allocated on a capturing stream) counts
+// directly too.
+stt_status count_louder(stt_ctx *c, const uint64_t *ref, int64_t n_ref, const uint64_t *q, int64_t n_q, int64_t *count,
+                        float *fap)
+{
+    const int64_t per_pass = (int64_t)kRankTile * kRankTiles;
+    const size_t need = sizeof(RankTile) * (size_t)std::min<int64_t>(kRankTiles, (n_q + kRankTile - 1) / kRankTile);
+    bool ranks = n_ref > kLouderDirect;
+    if (ranks && need > c->mdbuf_bytes) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) (void)hipGetLastError();
+        ranks = cs == hipStreamCaptureStatusNone && ensure_mdbuf(c, need) == STT_OK;
+    }
+    if (!ranks) {
+        hipLaunchKernelGGL(k_count_louder, dim3((unsigned)((n_q + 255) / 256)), dim3(256), 0, c->stream, ref, n_ref, q, n_q,
+                           count, fap, (double)n_ref);
+        STT_HIP(c, hipGetLastError());
+        return STT_OK;
+    }
+    RankTile *tiles = (RankTile *)c->mdbuf;
+    for (int64_t q0 = 0; q0 < n_q; q0 += per_pass) {
+        const int64_t m = std::min(per_pass, n_q - q0);
+        const unsigned nt = (unsigned)((m + kRankTile - 1) / kRankTile);
+        // 8 references per lane, at most four workgroups per CU over all tiles
+        const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n_ref + 8191) / 8192, 1024 / nt));
+        hipLaunchKernelGGL(k_rank_sort, dim3(nt), dim3(1024), 0, c->stream, q + q0, m, tiles);
+        hipLaunchKernelGGL(k_rank_count, dim3(nb, nt), dim3(1024), 0, c->stream, ref, n_ref, m, tiles);
+        hipLaunchKernelGGL(k_rank_finish, dim3(nt), dim3(1024), 0, c->stream, (const RankTile *)tiles, m,
+                           count ? count + q0 : nullptr, fap ? fap + q0 : nullptr, (double)n_ref);
+    }
+    STT_HIP(c, hipGetLastError());
+    return STT_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1171,24 +1230,7 @@ stt_status stt_topk(stt_ctx *c, const float *snr_dev, int64_t n, int64_t first, 
     if (K == 0) return STT_OK;
     if (!snr_dev || (!idx_dev && !val_dev)) return fail(c, STT_EINVAL, "snr_dev and an output must be non-NULL");
     STT_HIP(c, hipSetDevice(c->device));
-    const size_t st_bytes = (sizeof(TopkState) + 255) & ~(size_t)255;
-    if ((s = ensure_aux(c, st_bytes + sizeof(uint64_t) * (size_t)K)) != STT_OK) return s;
-    TopkState *st = (TopkState *)c->aux;
-    uint64_t *cand = (uint64_t *)((char *)c->aux + st_bytes);
-    const unsigned grid = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
-    hipLaunchKernelGGL(k_topk_init, dim3(1), dim3(256), 0, c->stream, st, (uint32_t)K);
-    for (int shift = 56; shift >= 0; shift -= 8) {
-        hipLaunchKernelGGL(k_topk_hist, dim3(grid), dim3(256), 0, c->stream, snr_dev, n, (uint64_t)first, st, shift);
-        hipLaunchKernelGGL(k_topk_pick, dim3(1), dim3(256), 0, c->stream, st, shift);
-    }
-    hipLaunchKernelGGL(k_topk_gather, dim3(grid), dim3(256), 0, c->stream, snr_dev, n, (uint64_t)first, st, cand,
-                       (uint32_t)K);
-    int P = 1;
-    while (P < K) P <<= 1;
-    hipLaunchKernelGGL(k_topk_sort, dim3(1), dim3(1024), sizeof(uint64_t) * P, c->stream, (const uint64_t *)cand, K,
-                       P, idx_dev, val_dev);
-    STT_HIP(c, hipGetLastError());
-    return STT_OK;
+    return topk_launch(c, TopkScores{snr_dev}, n, first, K, 0, idx_dev, val_dev);
 }
 
 stt_status stt_rescore_f64(stt_ctx *c, const stt_map *map, const stt_gen *gen, const stt_track *tracks_dev,
@@ -1242,20 +1284,11 @@ stt_status stt_significance(stt_ctx *c, const uint64_t *bg_keys_dev, int64_t n_b
     STT_HIP(c, hipSetDevice(c->device));
     stt_status s;
     if (n_fg > 0 && (n_louder_dev || fap_dev)) {
-        hipLaunchKernelGGL(k_count_louder, dim3((unsigned)((n_fg + 255) / 256)), dim3(256), 0, c->stream, bg_keys_dev,
-                           n_bg, fg_keys_dev, n_fg, n_louder_dev, fap_dev, (double)n_bg);
-        STT_HIP(c, hipGetLastError());
+        if ((s = count_louder(c, bg_keys_dev, n_bg, fg_keys_dev, n_fg, n_louder_dev, fap_dev)) != STT_OK) return s;
     }
-    if (z_alpha_dev) {
-        // the m-th largest background score: decode the keys, select the top m, keep the last
-        if ((s = ensure_mdbuf(c, sizeof(float) * ((size_t)n_bg + (size_t)m))) != STT_OK) return s;
-        float *scores = (float *)c->mdbuf;
-        float *top = scores + n_bg;
-        hipLaunchKernelGGL(k_key_scores, dim3((unsigned)((n_bg + 255) / 256)), dim3(256), 0, c->stream, bg_keys_dev,
-                           n_bg, scores);
-        STT_HIP(c, hipGetLastError());
-        if ((s = stt_topk(c, scores, n_bg, 0, m, nullptr, top)) != STT_OK) return s;
-        STT_HIP(c, hipMemcpyAsync(z_alpha_dev, top + (m - 1), sizeof(float), hipMemcpyDeviceToDevice, c->stream));
+    if (z_alpha_dev) {  // the m-th largest background score
+        if ((s = check_range(c, 0, n_bg)) != STT_OK) return s;
+        return topk_launch(c, TopkKeys{bg_keys_dev}, n_bg, 0, m, 1, nullptr, z_alpha_dev);
     }
     return STT_OK;
 }
@@ -1282,10 +1315,7 @@ stt_status stt_follow_up(stt_ctx *c, const stt_map *maps_host, int32_t n_maps, u
     // rank of map m = the number of maps at least as loud, itself included (as stt_significance counts)
     if ((s = ensure_aux(c, sizeof(int64_t) * (size_t)n_maps)) != STT_OK) return s;
     int64_t *rank_dev = (int64_t *)c->aux;
-    hipLaunchKernelGGL(k_count_louder, dim3((unsigned)((n_maps + 255) / 256)), dim3(256), 0, c->stream,
-                       (const uint64_t *)keys_dev, (int64_t)n_maps, (const uint64_t *)keys_dev, (int64_t)n_maps,
-                       rank_dev, (float *)nullptr, 1.0);
-    STT_HIP(c, hipGetLastError());
+    if ((s = count_louder(c, keys_dev, n_maps, keys_dev, n_maps, rank_dev, nullptr)) != STT_OK) return s;
     std::vector<int64_t> rank((size_t)n_maps);
     STT_HIP(c, hipMemcpyAsync(rank.data(), rank_dev, sizeof(int64_t) * (size_t)n_maps, hipMemcpyDeviceToHost,
                               c->stream));

@@ -11,8 +11,8 @@
 //   k_score_slab    time-slab scorer: the workgroup copies slabs of consecutive
 //                   columns of the folded map into LDS (LDS DMA, double-buffered)
 //                   and every lane gathers its templates' pixels there
-//   k_score_direct  one lane per template, pixels gathered straight from the
-//                   map in global memory (small calls, very wide maps)
+//   k_score_direct, k_score_wave  one lane or one wave per template, pixels
+//                   gathered straight from global memory (small calls, very wide maps)
 //   k_reduce_keys   max of the slab scorer's per-workgroup best keys
 //   k_argmax        max/argmax of an existing score array
 // Reductions use the packed 64-bit key (score bits, ~index), so results do not
@@ -269,10 +269,20 @@ __device__ __forceinline__ int wave_max_i32(int v)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
+// Max of the keys of a workgroup of 256 lanes into *best: waves by shuffles, the four waves
+// through LDS, one atomic per workgroup. (Atomics on one address complete one after the other,
+// 11 ns each on gfx950: with one per wave, calls of one template per wave took 11.4 ns per template.)
 __device__ __forceinline__ void merge_key(uint64_t *best, uint64_t key)
 {
+    __shared__ uint64_t kmax[4];
+    if (!best) return;  // uniform over the launch
     key = wave_max_u64(key);
-    if (best && (threadIdx.x & 63) == 0 && key) atomicMax((unsigned long long *)best, (unsigned long long)key);
+    if ((threadIdx.x & 63) == 0) kmax[threadIdx.x >> 6] = key;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) key = kmax[w] > key ? kmax[w] : key;
+        if (key) atomicMax((unsigned long long *)best, (unsigned long long)key);
+    }
 }
 
 // z of a template from its FP64 sum S of terms in units of `scale` (2^e of an FP16 map, else 1).
@@ -357,8 +367,55 @@ __global__ __launch_bounds__(256) void k_make_tracks(GenP g, uint64_t first, int
     if (i < n) out[i] = draw_track(g, first + (uint64_t)i);
 }
 
-// ---------------------------------------------------------------- direct scorer
+// ---------------------------------------------------------------- direct scorers
+// Calls too small for the slab scorer, and maps too wide for it: pixels gathered straight from
+// global memory. Both scorers walk a template by flush groups (kFlush aligned columns): all rows of
+// a group first, then its 16 gathers, all in flight at once, then its terms in column order, so a
+// template costs one memory latency per group instead of one per column (search map, 20 000
+// templates: 297 us with a gather at a time). Columns of a group outside the template gather the
+// template's first pixel's column and drop the term.
 
+// Element e of the map a direct scorer reads, in the polar form of its terms: a folded map, an FP16
+// map's own words, or an FP32 map folded here (the expression of k_fold_polar, so the same bits).
+template <int MAPT> struct PolOf { using type = float2; };
+template <> struct PolOf<kMapPolH> { using type = uint32_t; };
+template <> struct PolOf<kMapP16> { using type = uint32_t; };
+template <int MAPT> using pol_t = typename PolOf<MAPT>::type;
+
+template <int MAPT>
+__device__ __forceinline__ pol_t<MAPT> load_pol(const MapP &m, int64_t e)
+{
+    if constexpr (MAPT == kMapPolH || MAPT == kMapP16) return reinterpret_cast<const uint32_t *>(m.Y)[e];
+    else if constexpr (MAPT == kMapF32) return polar_of(load_p<kMapF32>(m, e));
+    else return m.Y[e];
+}
+
+// The FP32 sum of a template's terms over the flush group that starts at column cb (a multiple of
+// kFlush), for a row walk st standing at cb; st is advanced past the group. t0 .. t2: its columns.
+template <bool HW, int MAPT>
+__device__ __forceinline__ float group_sum(const MapP &m, const PhaseK &pk, int32_t cb, int32_t t0, int32_t t2, DdaF &st)
+{
+    int32_t row[kFlush];
+    pol_t<MAPT> v[kFlush];
+#pragma unroll
+    for (int j = 0; j < kFlush; ++j) {
+        const int32_t c = cb + j;
+        const bool act = c >= t0 && c <= t2;
+        row[j] = act ? ddaf_row(st) : 0;
+        v[j] = load_pol<MAPT>(m, (int64_t)(act ? c : t0) * m.ld + row[j]);
+        ddaf_step(st);
+    }
+    float part = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kFlush; ++j) {
+        const int32_t c = cb + j;
+        const float p = add_term_pol<HW>(part, pk, row[j], v[j]);
+        part = c >= t0 && c <= t2 ? p : part;
+    }
+    return part;
+}
+
+// One lane per template.
 template <bool EXPL, bool HW, int MAPT>
 __global__ __launch_bounds__(kWG) void k_score_direct(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n,
                                                       int32_t norm, float *snr, uint64_t *best)
@@ -369,21 +426,12 @@ __global__ __launch_bounds__(kWG) void k_score_direct(MapP m, GenP g, const Trk 
         const Trk t = EXPL ? tr[i] : draw_track(g, first + (uint64_t)i);
         float z = __builtin_nanf("");
         if (!EXPL || track_ok(t, m)) {
-            DdaF s = ddaf_init_at(t, 0);
             const PhaseK pk = phase_k(m, t.dtau);
-            const int32_t N = t.t2 - t.t0 + 1;
-            int64_t base = (int64_t)t.t0 * m.ld;
+            int32_t cb = t.t0 & ~(kFlush - 1);
+            DdaF st = ddaf_init_at(t, cb - t.t0);
             double acc = 0.0;
-            float part = 0.0f;
-            for (int32_t k = 0; k < N; ++k) {
-                const int32_t row = ddaf_row(s);
-                const elem_t<MAPT> p = load_e<MAPT>(m, base + row);
-                part = add_term_m<HW, MAPT>(part, pk, row, p);
-                if (((t.t0 + k) & (kFlush - 1)) == kFlush - 1) { acc += part; part = 0.0f; }
-                ddaf_step(s);
-                base += m.ld;
-            }
-            z = finish(acc + part, N, norm, m.scale);
+            for (; cb <= t.t2; cb += kFlush) acc += group_sum<HW, MAPT>(m, pk, cb, t.t0, t.t2, st);
+            z = finish(acc, t.t2 - t.t0 + 1, norm, m.scale);
         }
         if (snr) snr[i] = z;
         key = key_encode(z, (uint32_t)(first + (uint64_t)i));
@@ -392,23 +440,33 @@ __global__ __launch_bounds__(kWG) void k_score_direct(MapP m, GenP g, const Trk 
 }
 
 // One wave per template, for calls too small to fill the chip with one lane
-// per template. The template's columns fall into flush groups of kFlush
-// aligned columns; lane l takes groups l, l + 64, ... and computes each
-// group's FP32 partial with the same operations, in the same order, as the
-// sequential walk of k_score_direct. The FP64 sum over groups then runs in
-// column order (read lane by lane), so the score is bit-identical to the other
-// scorers'. Four waves (templates) per workgroup.
+// per template: lane l takes the template's groups l, l + 64, ... The FP64 sum
+// over groups runs in column order (read lane by lane), so the score is
+// bit-identical to the other scorers'. Four waves (templates at a time) per
+// workgroup, which strides over the templates.
 constexpr int kWaveGroups = (STT_MAX_T + kFlush - 1) / kFlush + 1;  // groups a template can touch
 constexpr int kWaveRounds = (kWaveGroups + 63) / 64;
+
+// The sum in order of gp[r] of lanes 0 .. over rounds r: ng group sums.
+__device__ __forceinline__ double wave_ordered_sum(const float (&gp)[kWaveRounds], int ng)
+{
+    double acc = 0.0;
+#pragma unroll
+    for (int r = 0; r < kWaveRounds; ++r) {
+        const int cnt = min(64, ng - r * 64);
+        for (int l = 0; l < cnt; ++l)
+            acc += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gp[r]), l));
+    }
+    return acc;
+}
 
 template <bool EXPL, bool HW, int MAPT>
 __global__ __launch_bounds__(256) void k_score_wave(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n,
                                                     int32_t norm, float *snr, uint64_t *best)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // wave-uniform
     uint64_t key = 0;
-    if (i < n) {
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {  // wave-uniform
         const Trk t = EXPL ? tr[i] : draw_track(g, first + (uint64_t)i);
         float z = __builtin_nanf("");
         if (!EXPL || track_ok(t, m)) {
@@ -420,34 +478,14 @@ __global__ __launch_bounds__(256) void k_score_wave(MapP m, GenP g, const Trk *t
                 gp[r] = 0.0f;
                 const int gi = gfirst + r * 64 + lane;
                 if (gi > glast) continue;
-                const int ca = max(t.t0, gi * kFlush), cb = min(t.t2, gi * kFlush + kFlush - 1);
-                DdaF s = ddaf_init_at(t, ca - t.t0);
-                int64_t base = (int64_t)ca * m.ld;
-                float part = 0.0f;
-                for (int c = ca; c <= cb; ++c) {
-                    const int32_t row = ddaf_row(s);
-                    part = add_term_m<HW, MAPT>(part, pk, row, load_e<MAPT>(m, base + row));
-                    ddaf_step(s);
-                    base += m.ld;
-                }
-                gp[r] = part;
+                DdaF st = ddaf_init_at(t, gi * kFlush - t.t0);
+                gp[r] = group_sum<HW, MAPT>(m, pk, gi * kFlush, t.t0, t.t2, st);
             }
-            // The sequential walk adds each group's partial to acc, in order: at the group's flush
-            // column, or (the last group, when t2 is not a flush column) as finish(acc + part);
-            // a flushed last group leaves part = 0 for that final addition.
-            const int ng = glast - gfirst + 1;
-            double acc = 0.0;
-#pragma unroll
-            for (int r = 0; r < kWaveRounds; ++r) {
-                const int cnt = min(64, ng - r * 64);
-                for (int l = 0; l < cnt; ++l)
-                    acc += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gp[r]), l));
-            }
-            if ((t.t2 & (kFlush - 1)) == kFlush - 1) acc = acc + 0.0f;
-            z = finish(acc, t.t2 - t.t0 + 1, norm, m.scale);
+            z = finish(wave_ordered_sum(gp, glast - gfirst + 1), t.t2 - t.t0 + 1, norm, m.scale);
         }
         if (lane == 0 && snr) snr[i] = z;
-        key = key_encode(z, (uint32_t)(first + (uint64_t)i));
+        const uint64_t k = key_encode(z, (uint32_t)(first + (uint64_t)i));
+        key = k > key ? k : key;
     }
     merge_key(best, key);
 }
@@ -1378,14 +1416,14 @@ __global__ __launch_bounds__(256) void k_make_tracks_tm(GenP g, uint64_t first, 
     if (i < n) out[i] = draw_track_tm(g, first + (uint64_t)i);
 }
 
+// A wave per template, lanes over flush groups (as k_score_wave, with an independent row per column).
 template <bool EXPL, bool HW, int MAPT>
 __global__ __launch_bounds__(256) void k_score_tm(MapP m, GenP g, const TrkTm *tr, uint64_t first, int64_t n,
                                                   int32_t norm, float *snr, uint64_t *best)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // wave-uniform
     uint64_t key = 0;
-    if (i < n) {
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {  // wave-uniform
         const TrkTm t = EXPL ? tr[i] : draw_track_tm(g, first + (uint64_t)i);
         float z = __builtin_nanf("");
         if (!EXPL || track_tm_ok(t, m)) {
@@ -1398,37 +1436,34 @@ __global__ __launch_bounds__(256) void k_score_tm(MapP m, GenP g, const TrkTm *t
                 gp[r] = 0.0f;
                 const int gi = gfirst + r * 64 + lane;
                 if (gi > glast) continue;
-                const int ca = max(t.t0, gi * kFlush), cb = min(t.t2, gi * kFlush + kFlush - 1);
+                int32_t row[kFlush];
+                pol_t<MAPT> v[kFlush];
+#pragma unroll
+                for (int j = 0; j < kFlush; ++j) {
+                    const int32_t c = min(max(gi * kFlush + j, t.t0), t.t2);
+                    bool ok;
+                    row[j] = row_tm_fp32(k, c - t.t0, ok);
+                    if (!ok) row[j] = row_tm_fallback(k, c - t.t0);
+                    v[j] = load_pol<MAPT>(m, (int64_t)c * m.ld + row[j]);
+                }
                 float part = 0.0f;
-                for (int c = ca; c <= cb; ++c) {
-                    const int32_t row = row_tm(k, c - t.t0);
-                    part = add_term_m<HW, MAPT>(part, pk, row, load_e<MAPT>(m, (int64_t)c * m.ld + row));
+#pragma unroll
+                for (int j = 0; j < kFlush; ++j) {
+                    const int32_t c = gi * kFlush + j;
+                    const float p = add_term_pol<HW>(part, pk, row[j], v[j]);
+                    part = c >= t.t0 && c <= t.t2 ? p : part;
                 }
                 gp[r] = part;
             }
-            const int ng = glast - gfirst + 1;
-            double acc = 0.0;
-#pragma unroll
-            for (int r = 0; r < kWaveRounds; ++r) {
-                const int cnt = min(64, ng - r * 64);
-                for (int l = 0; l < cnt; ++l)
-                    acc += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gp[r]), l));
-            }
-            if ((t.t2 & (kFlush - 1)) == kFlush - 1) acc = acc + 0.0f;
-            z = finish(acc, t.t2 - t.t0 + 1, norm, m.scale);
+            z = finish(wave_ordered_sum(gp, glast - gfirst + 1), t.t2 - t.t0 + 1, norm, m.scale);
         }
         if (lane == 0 && snr) snr[i] = z;
-        key = key_encode(z, (uint32_t)(first + (uint64_t)i));
+        const uint64_t k = key_encode(z, (uint32_t)(first + (uint64_t)i));
+        key = k > key ? k : key;
     }
     merge_key(best, key);
 }
 
-// Column walk of the free-t_mid slab scorer (as walk, with an independent row per column). The
-// FP32 pass takes every template's row of the column, with D = b^2 + 4 a dt and 2 dt carried from
-// column to column by one add each; where it does not stand for some lane (about one template
-// pixel in a thousand on the search band), the whole wave takes one uniform branch in which those
-// lanes settle their rows exactly. A lane outside its template's columns works on column t0 + 1
-// (valid for every template) and drops the term.
 // Column walk of the free-t_mid slab scorer (as walk, with an independent row per column). The
 // FP32 pass takes every template's row of the column, with D = b^2 + 4 a dt and 2 dt carried from
 // column to column by one add each (Dc, dt2c: their values at column ca, advanced past cb on
@@ -1680,7 +1715,32 @@ __device__ __forceinline__ void merge_running(float &z, int32_t &mi, float zp, i
     if (!(z > zp)) { z = zp; mi = mp; }
 }
 
-// One lane per template, direct gathers (small calls, maps too wide for LDS).
+// The FP32 sums, for the launch's delays, of a template's terms over the flush group that starts at
+// column cb, for a row walk standing there (as group_sum).
+template <bool HW, int MAPT>
+__device__ __forceinline__ void group_sums_md(const MapP &m, const DelayGrid &dg, int32_t cb, int32_t t0, int32_t t2,
+                                              DdaF &st, float (&part)[kMD])
+{
+    int32_t row[kFlush];
+    pol_t<MAPT> v[kFlush];
+#pragma unroll
+    for (int j = 0; j < kFlush; ++j) {
+        const int32_t c = cb + j;
+        const bool act = c >= t0 && c <= t2;
+        row[j] = act ? ddaf_row(st) : 0;
+        v[j] = load_pol<MAPT>(m, (int64_t)(act ? c : t0) * m.ld + row[j]);
+        ddaf_step(st);
+    }
+#pragma unroll
+    for (int k = 0; k < kMD; ++k) part[k] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kFlush; ++j) {
+        const int32_t c = cb + j;
+        add_terms_md<HW, true>(part, dg, row[j], v[j], c >= t0 && c <= t2);
+    }
+}
+
+// One lane per template, direct gathers (maps too wide for LDS, medium calls).
 template <bool EXPL, bool HW, int MAPT>
 __global__ __launch_bounds__(kWG) void k_score_md_direct(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n,
                                                          int32_t norm, int32_t d0, int32_t step, int32_t m0,
@@ -1697,29 +1757,80 @@ __global__ __launch_bounds__(kWG) void k_score_md_direct(MapP m, GenP g, const T
         float part[kMD];
 #pragma unroll
         for (int k = 0; k < kMD; ++k) { acc[k] = 0.0; part[k] = 0.0f; }
-        const int32_t N = t.t2 - t.t0 + 1;
         if (ok) {
-            DdaF s = ddaf_init_at(t, 0);
-            int64_t base = (int64_t)t.t0 * m.ld;
-            for (int32_t k = 0; k < N; ++k) {
-                const int32_t row = ddaf_row(s);
-                const elem_t<MAPT> p = load_e<MAPT>(m, base + row);
-                add_terms_md<HW, false>(part, dg, row, p, true);
-                if (((t.t0 + k) & (kFlush - 1)) == kFlush - 1) {
+            int32_t cb = t.t0 & ~(kFlush - 1);
+            DdaF st = ddaf_init_at(t, cb - t.t0);
+            for (; cb <= t.t2; cb += kFlush) {
+                group_sums_md<HW, MAPT>(m, dg, cb, t.t0, t.t2, st, part);
 #pragma unroll
-                    for (int q = 0; q < kMD; ++q) { acc[q] += part[q]; part[q] = 0.0f; }
-                }
-                ddaf_step(s);
-                base += m.ld;
+                for (int q = 0; q < kMD; ++q) { acc[q] += part[q]; part[q] = 0.0f; }
             }
         }
         float z;
         int32_t mi;
-        merge_delays(acc, part, N, norm, m.scale, dg, ok, z, mi);
+        merge_delays(acc, part, t.t2 - t.t0 + 1, norm, m.scale, dg, ok, z, mi);
         merge_running(z, mi, m0 ? snr[i] : 0.0f, m0 ? tidx[i] : 0, m0 == 0);
         snr[i] = z;
         tidx[i] = mi;
         if (last) key = key_encode(z, (uint32_t)(first + (uint64_t)i));
+    }
+    if (last) merge_key(best, key);
+}
+
+// One wave per template for small calls: lanes over flush groups as k_score_wave, each group's kMD
+// partial sums through LDS to kMD lanes, which add them in column order (the same bits as the other
+// scorers). Four waves per workgroup, which strides over the templates.
+template <bool EXPL, bool HW, int MAPT>
+__global__ __launch_bounds__(256) void k_score_md_wave(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n,
+                                                       int32_t norm, int32_t d0, int32_t step, int32_t m0, int32_t cnt,
+                                                       int32_t last, float *snr, int32_t *tidx, uint64_t *best)
+{
+    __shared__ float gsum[4][64][kMD + 1];  // one round of groups per wave; padded rows spread the banks
+    const DelayGrid dg = delay_grid(m, d0, step, m0, cnt);
+    const int lane = threadIdx.x & 63;
+    float (*gs)[kMD + 1] = gsum[threadIdx.x >> 6];
+    uint64_t key = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += (int64_t)gridDim.x * 4) {  // wave-uniform
+        const Trk t = EXPL ? tr[i] : draw_track(g, first + (uint64_t)i);
+        float z = __builtin_nanf("");
+        int32_t mi = -1;
+        if (!EXPL || track_ok(t, m)) {
+            const int gfirst = t.t0 / kFlush, glast = t.t2 / kFlush;
+            double acc = 0.0;  // of delay `lane` in lanes 0 .. kMD - 1
+            for (int r0 = gfirst; r0 <= glast; r0 += 64) {
+                const int gi = r0 + lane;
+                if (gi <= glast) {
+                    DdaF st = ddaf_init_at(t, gi * kFlush - t.t0);
+                    float part[kMD];
+                    group_sums_md<HW, MAPT>(m, dg, gi * kFlush, t.t0, t.t2, st, part);
+#pragma unroll
+                    for (int q = 0; q < kMD; ++q) gs[lane][q] = part[q];
+                }
+                __builtin_amdgcn_wave_barrier();
+                if (lane < kMD)
+                    for (int l = 0; l < min(64, glast - r0 + 1); ++l) acc += gs[l][lane];
+                __builtin_amdgcn_wave_barrier();
+            }
+            const int32_t N = t.t2 - t.t0 + 1;
+            const float v = lane < dg.cnt ? finish(acc, N, norm, m.scale) : -__builtin_inff();
+            if (!__builtin_amdgcn_ballot_w64(v != v)) {
+                // largest score, then lowest delay: the scores' ordered bits with the delay's complement
+                const uint64_t kq = lane < dg.cnt ? key_encode(v, (uint32_t)lane) : 0;
+                const uint64_t top = wave_max_u64(kq);
+                mi = (int32_t)(0xFFFFFFFFu - (uint32_t)top);
+                z = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), mi));
+                mi += dg.m0;
+            }
+        }
+        merge_running(z, mi, m0 ? snr[i] : 0.0f, m0 ? tidx[i] : 0, m0 == 0);
+        if (lane == 0) {
+            snr[i] = z;
+            tidx[i] = mi;
+        }
+        if (last) {
+            const uint64_t k = key_encode(z, (uint32_t)(first + (uint64_t)i));
+            key = k > key ? k : key;
+        }
     }
     if (last) merge_key(best, key);
 }

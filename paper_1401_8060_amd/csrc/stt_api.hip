@@ -373,18 +373,40 @@ stt_status launch_slab(stt_ctx *c, int sc, int wg, int tpt, const MapP &m, const
     }
 }
 
+// Workgroups of a wave-per-template launch (four templates at a time each, striding over the rest):
+// 16 waves per CU, and at most 1024 atomics on the best key, one per workgroup.
+unsigned wave_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 3) / 4, 1024); }
+
 template <bool EXPL, bool HW, int MAPT>
 void launch_direct(stt_ctx *c, bool per_wave, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n,
                    int32_t norm, float *snr, uint64_t *best)
 {
     if (per_wave) {
-        hipLaunchKernelGGL((k_score_wave<EXPL, HW, MAPT>), dim3((unsigned)((n + 3) / 4)), dim3(256), 0, c->stream, m,
-                           g, tr, (uint64_t)first, n, norm, snr, best);
+        hipLaunchKernelGGL((k_score_wave<EXPL, HW, MAPT>), dim3(wave_grid(n)), dim3(256), 0, c->stream, m, g, tr,
+                           (uint64_t)first, n, norm, snr, best);
         return;
     }
     const unsigned grid = (unsigned)((n + kWG - 1) / kWG);
     hipLaunchKernelGGL((k_score_direct<EXPL, HW, MAPT>), dim3(grid), dim3(kWG), 0, c->stream, m, g, tr,
                        (uint64_t)first, n, norm, snr, best);
+}
+
+// The direct scorers of one call on map m (format MAPT: kMapPol, kMapF32 or kMapP16), timed as the
+// scoring stage.
+template <bool EXPL, int MAPT>
+stt_status score_direct(stt_ctx *c, bool per_wave, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n,
+                        int32_t norm, float *snr, uint64_t *best)
+{
+    ev_record(c, 0);
+    if (c->hw_trig)
+        launch_direct<EXPL, true, MAPT>(c, per_wave, m, g, tr, first, n, norm, snr, best);
+    else
+        launch_direct<EXPL, false, MAPT>(c, per_wave, m, g, tr, first, n, norm, snr, best);
+    STT_HIP(c, hipGetLastError());
+    ev_record(c, 1);
+    ev_record(c, 5);
+    c->used[0] = true;
+    return STT_OK;
 }
 
 // Work memory handed to a scoring call instead of the context's own (which grows
@@ -511,25 +533,13 @@ stt_status bin_templates(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr
     return STT_OK;
 }
 
-// The scorers of one call on the folded map m (format MAPT: kMapPol or kMapPolH).
+// The slab scorer of one call on the folded map m (format MAPT: kMapPol or kMapPolH).
 template <bool EXPL, int MAPT>
-stt_status score_folded(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n,
-                        int32_t norm, float *snr, uint64_t *best, const FixedBufs *fb, bool slab, bool per_wave)
+stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n, int32_t norm,
+                       float *snr, uint64_t *best, const FixedBufs *fb)
 {
     constexpr int esize = (int)sizeof(elem_t<MAPT>);
     stt_status s;
-    if (!slab) {
-        ev_record(c, 0);
-        if (c->hw_trig)
-            launch_direct<EXPL, true, MAPT>(c, per_wave, m, g, tr, first, n, norm, snr, best);
-        else
-            launch_direct<EXPL, false, MAPT>(c, per_wave, m, g, tr, first, n, norm, snr, best);
-        STT_HIP(c, hipGetLastError());
-        ev_record(c, 1);
-        ev_record(c, 5);
-        c->used[0] = true;
-        return STT_OK;
-    }
     uint32_t *order = nullptr;
     uint64_t *wg_keys = nullptr;
     if ((s = bin_templates<EXPL>(c, m, g, tr, first, n, fb, order, wg_keys)) != STT_OK) return s;
@@ -560,6 +570,27 @@ stt_status score_folded(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr,
     return STT_OK;
 }
 
+// Wave-per-template calls whose templates together hold fewer pixels than the map gather from the
+// caller's FP32 map and form the polar elements as they go; others fold the map first (9 us for 1000
+// x 1000). A template holds up to T pixels, so n <= F keeps the gathers below the map's T x F
+// pixels. One lane per template always folds: its polar forms would follow one another (326 us
+// folded, 629 us not, for 1000 templates on 1000 x 1000). FP16 maps are gathered as they are by
+// every direct scorer: their words are the polar elements.
+bool gather_unfolded(const stt_map *map, bool per_wave, int64_t n)
+{
+    return map->dtype == STT_P16 || (per_wave && n <= map->F);
+}
+
+// Which scorer takes a call of n templates on T columns. The slab scorer sweeps the columns one slab
+// after the other, so a small call costs it a floor that grows with T (58, 98, 203, 490 us at T = 100,
+// 500, 1000, 2000 with F = 128, 151, 1000, 2000); the direct scorers' cost grows with the pixels.
+// They cross near n T = 6e7 pixels' worth: at T = 300, 63 and 80 us for 10^5 templates, 140 and 79 for
+// 3 x 10^5; at T = 1000, 100 and 203 us for 4 x 10^4, 223 and 203 for 10^5. Below that, one wave per
+// template costs 1.1 + T/900 ns each, one lane per template at least the longest template's walk
+// (0.11-0.16 us per column), which cross near n = 80000 T / (T + 600).
+bool prefer_slabs(int T, int64_t n) { return n >= 4096 && n * (int64_t)T >= 60000000; }
+bool prefer_wave(int T, int64_t n) { return n * (int64_t)(T + 600) < 80000 * (int64_t)T; }
+
 template <bool EXPL>
 stt_status score_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Trk *tr, int64_t first, int64_t n,
                       int32_t norm, float *snr, uint64_t *best, const FixedBufs *fb = nullptr)
@@ -568,20 +599,28 @@ stt_status score_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Trk *
     // the slab plus the kernel's few static LDS words must fit the 160 KB of a CU
     bool slab = (c->lds_bytes - 256) / (esize * F) >= 1;
     if (c->path == 1 || c->path == 3) slab = false;
-    if (c->path == 0 && n < 4096) slab = false;
-    // without slabs: one wave per template for calls too small to fill the chip lane by lane
-    const bool per_wave = c->path == 3 || (c->path == 0 && n < 65536);
+    if (c->path == 0 && !prefer_slabs(map->T, n)) slab = false;
+    const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave(map->T, n));
     if (c->path == 2 && !slab)
         return fail(c, STT_EUNSUPPORTED, "F=%d too wide for an LDS slab of %d bytes", F, c->lds_bytes);
 
     stt_status s = ev_begin(c);
     if (s != STT_OK) return s;
-    ev_attach(c, 4, -1);  // taken by the fold's launch
-    MapP m;
-    if ((s = fold_polar(c, map, fb, m)) != STT_OK) return s;
-    // score_folded records event 5 at the end of its last kernel
-    s = map->dtype == STT_P16 ? score_folded<EXPL, kMapPolH>(c, m, g, tr, first, n, norm, snr, best, fb, slab, per_wave)
-                              : score_folded<EXPL, kMapPol>(c, m, g, tr, first, n, norm, snr, best, fb, slab, per_wave);
+    const bool p16 = map->dtype == STT_P16;
+    // score_slabs and score_direct record event 5 at the end of their last kernel
+    if (!slab && gather_unfolded(map, per_wave, n)) {
+        ev_record(c, 4);
+        const MapP m = to_mapp(map);
+        s = p16 ? score_direct<EXPL, kMapP16>(c, per_wave, m, g, tr, first, n, norm, snr, best)
+                : score_direct<EXPL, kMapF32>(c, per_wave, m, g, tr, first, n, norm, snr, best);
+    } else {
+        ev_attach(c, 4, -1);  // taken by the fold's launch
+        MapP m;
+        if ((s = fold_polar(c, map, fb, m)) != STT_OK) return s;
+        s = !slab ? score_direct<EXPL, kMapPol>(c, per_wave, m, g, tr, first, n, norm, snr, best)
+            : p16 ? score_slabs<EXPL, kMapPolH>(c, m, g, tr, first, n, norm, snr, best, fb)
+                  : score_slabs<EXPL, kMapPol>(c, m, g, tr, first, n, norm, snr, best, fb);
+    }
     if (s != STT_OK) return s;
     c->used[2] = true;
     ev_end(c);
@@ -618,13 +657,35 @@ stt_status fold_polar(stt_ctx *c, const stt_map *map, const FixedBufs *fb, MapP 
     return STT_OK;
 }
 
-// The delay grid in launches of kMD delays. Slabs (binned templates, folded map,
-// LDS-DMA) from 4096 templates on when two slabs of a column fit; otherwise one
-// lane per template with direct gathers. Both give bit-identical results.
+// The delay grid in launches of kMD delays by the direct scorers, one wave or one lane per template,
+// on map m (format MAPT: kMapPol, kMapF32 or kMapP16).
 template <bool EXPL, int MAPT>
-stt_status maxdelay_folded(stt_ctx *c, const MapP &mf, const GenP &g, const Trk *tr, int64_t first, int64_t n,
-                           int32_t d0, int32_t step, int32_t n_tau, int32_t norm, float *snr, int32_t *tidx,
-                           uint64_t *best, bool slab, int lds)
+stt_status maxdelay_direct(stt_ctx *c, bool per_wave, const MapP &m, const GenP &g, const Trk *tr, int64_t first,
+                           int64_t n, int32_t d0, int32_t step, int32_t n_tau, int32_t norm, float *snr, int32_t *tidx,
+                           uint64_t *best)
+{
+    const int n_launch = (n_tau + kMD - 1) / kMD;
+    const unsigned grid = per_wave ? wave_grid(n) : (unsigned)((n + kWG - 1) / kWG);
+    auto kern = per_wave ? (c->hw_trig ? k_score_md_wave<EXPL, true, MAPT> : k_score_md_wave<EXPL, false, MAPT>)
+                         : (c->hw_trig ? k_score_md_direct<EXPL, true, MAPT> : k_score_md_direct<EXPL, false, MAPT>);
+    ev_record(c, 0);
+    for (int l = 0; l < n_launch; ++l) {
+        const int32_t m0 = l * kMD, cnt = std::min(kMD, n_tau - m0), last = l == n_launch - 1;
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, c->stream, m, g, tr, (uint64_t)first, n, norm, d0, step, m0,
+                           cnt, last, snr, tidx, best);
+    }
+    STT_HIP(c, hipGetLastError());
+    ev_record(c, 1);
+    c->used[0] = true;
+    return STT_OK;
+}
+
+// The delay grid in launches of kMD delays from slabs (binned templates, folded map, LDS-DMA). The
+// same bits as the direct scorers.
+template <bool EXPL, int MAPT>
+stt_status maxdelay_slabs(stt_ctx *c, const MapP &mf, const GenP &g, const Trk *tr, int64_t first, int64_t n,
+                          int32_t d0, int32_t step, int32_t n_tau, int32_t norm, float *snr, int32_t *tidx,
+                          uint64_t *best, int lds)
 {
     // 1024 lanes x 1 template, at most 80 KB of slabs (measured on the search map: 512 x 2, 1024 x 2,
     // 256 x 4 and smaller slabs were 15-75 % slower; one template per lane leaves room for more waves)
@@ -633,23 +694,6 @@ stt_status maxdelay_folded(stt_ctx *c, const MapP &mf, const GenP &g, const Trk 
     const int64_t ldc = mf.ld;
     const int n_launch = (n_tau + kMD - 1) / kMD;
     stt_status s;
-    if (!slab) {
-        ev_record(c, 0);
-        const unsigned grid = (unsigned)((n + kWG - 1) / kWG);
-        for (int l = 0; l < n_launch; ++l) {
-            const int32_t m0 = l * kMD, cnt = std::min(kMD, n_tau - m0), last = l == n_launch - 1;
-            if (c->hw_trig)
-                hipLaunchKernelGGL((k_score_md_direct<EXPL, true, MAPT>), dim3(grid), dim3(kWG), 0, c->stream, mf, g,
-                                   tr, (uint64_t)first, n, norm, d0, step, m0, cnt, last, snr, tidx, best);
-            else
-                hipLaunchKernelGGL((k_score_md_direct<EXPL, false, MAPT>), dim3(grid), dim3(kWG), 0, c->stream, mf,
-                                   g, tr, (uint64_t)first, n, norm, d0, step, m0, cnt, last, snr, tidx, best);
-        }
-        STT_HIP(c, hipGetLastError());
-        ev_record(c, 1);
-        c->used[0] = true;
-        return STT_OK;
-    }
     uint32_t *order = nullptr;
     uint64_t *wg_keys = nullptr;
     if ((s = bin_templates<EXPL>(c, mf, g, tr, first, n, nullptr, order, wg_keys)) != STT_OK) return s;
@@ -698,11 +742,19 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     }
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
-    MapP mf;
-    if ((s = fold_polar(c, map, nullptr, mf)) != STT_OK) return s;
-    s = map->dtype == STT_P16
-            ? maxdelay_folded<EXPL, kMapPolH>(c, mf, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best, slab, lds)
-            : maxdelay_folded<EXPL, kMapPol>(c, mf, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best, slab, lds);
+    const bool p16 = map->dtype == STT_P16;
+    const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave(map->T, n));
+    if (!slab && gather_unfolded(map, per_wave, n * ((n_tau + kMD - 1) / kMD))) {
+        const MapP m = to_mapp(map);
+        s = p16 ? maxdelay_direct<EXPL, kMapP16>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best)
+                : maxdelay_direct<EXPL, kMapF32>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best);
+    } else {
+        MapP mf;
+        if ((s = fold_polar(c, map, nullptr, mf)) != STT_OK) return s;
+        s = !slab ? maxdelay_direct<EXPL, kMapPol>(c, per_wave, mf, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best)
+            : p16 ? maxdelay_slabs<EXPL, kMapPolH>(c, mf, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best, lds)
+                  : maxdelay_slabs<EXPL, kMapPol>(c, mf, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best, lds);
+    }
     if (s != STT_OK) return s;
     ev_record(c, 5);
     c->used[2] = true;
@@ -710,48 +762,47 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     return STT_OK;
 }
 
-// The free-t_mid scorers of one call on the folded map mf (format MAPT).
+// The free-t_mid slab scorer of one call on the folded map mf (format MAPT: kMapPol or kMapPolH).
 template <int MAPT>
-stt_status score_tm_folded(stt_ctx *c, const MapP &mf, const GenP &g, const TrkTm *tr, int64_t first, int64_t n,
-                           int32_t norm, float *snr_dev, uint64_t *best_key_dev, bool slab, int lds)
+stt_status score_tm_slabs(stt_ctx *c, const MapP &mf, const GenP &g, int64_t first, int64_t n, int32_t norm,
+                          float *snr_dev, uint64_t *best_key_dev, int lds)
 {
     constexpr int kTmWG = 1024, kTmTPT = 1;
     constexpr int esize = (int)sizeof(elem_t<MAPT>);
     stt_status s;
-    if (slab) {
-        uint32_t *order = nullptr;
-        uint64_t *wg_keys = nullptr;
-        if ((s = bin_templates<false>(c, mf, g, nullptr, first, n, nullptr, order, wg_keys)) != STT_OK) return s;
-        const int S = std::min(dma_slab_cols(lds, mf.ld, esize), mf.T);
-        const size_t shm = 2 * (size_t)esize * (size_t)S * mf.ld;
-        const unsigned grid = (unsigned)((n + kTmWG * kTmTPT - 1) / (kTmWG * kTmTPT));
-        auto kern = c->hw_trig ? k_score_tm_slab<kTmWG, kTmTPT, true, MAPT> : k_score_tm_slab<kTmWG, kTmTPT, false, MAPT>;
-        if (shm > 64 * 1024)
-            STT_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
-        ev_record(c, 0);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kTmWG), shm, c->stream, mf, g, (const uint32_t *)order,
-                           (uint64_t)first, n, S, norm, snr_dev, wg_keys);
-        STT_HIP(c, hipGetLastError());
-        ev_record(c, 1);
-        c->used[0] = true;
-        if (best_key_dev) {
-            hipLaunchKernelGGL(k_reduce_keys, dim3(1), dim3(1024), 0, c->stream, (const uint64_t *)wg_keys,
-                               (int64_t)grid, best_key_dev);
-            STT_HIP(c, hipGetLastError());
-        }
-        return STT_OK;
-    }
-    const dim3 grid((unsigned)((n + 3) / 4)), block(256);
+    uint32_t *order = nullptr;
+    uint64_t *wg_keys = nullptr;
+    if ((s = bin_templates<false>(c, mf, g, nullptr, first, n, nullptr, order, wg_keys)) != STT_OK) return s;
+    const int S = std::min(dma_slab_cols(lds, mf.ld, esize), mf.T);
+    const size_t shm = 2 * (size_t)esize * (size_t)S * mf.ld;
+    const unsigned grid = (unsigned)((n + kTmWG * kTmTPT - 1) / (kTmWG * kTmTPT));
+    auto kern = c->hw_trig ? k_score_tm_slab<kTmWG, kTmTPT, true, MAPT> : k_score_tm_slab<kTmWG, kTmTPT, false, MAPT>;
+    if (shm > 64 * 1024)
+        STT_HIP(c, hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
     ev_record(c, 0);
-#define STT_TM_LAUNCH(E, H)                                                                                     \
-    hipLaunchKernelGGL((k_score_tm<E, H, MAPT>), grid, block, 0, c->stream, mf, g, tr, (uint64_t)first, n, norm, \
-                       snr_dev, best_key_dev)
-    if (tr) {
-        if (c->hw_trig) STT_TM_LAUNCH(true, true); else STT_TM_LAUNCH(true, false);
-    } else {
-        if (c->hw_trig) STT_TM_LAUNCH(false, true); else STT_TM_LAUNCH(false, false);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kTmWG), shm, c->stream, mf, g, (const uint32_t *)order,
+                       (uint64_t)first, n, S, norm, snr_dev, wg_keys);
+    STT_HIP(c, hipGetLastError());
+    ev_record(c, 1);
+    c->used[0] = true;
+    if (best_key_dev) {
+        hipLaunchKernelGGL(k_reduce_keys, dim3(1), dim3(1024), 0, c->stream, (const uint64_t *)wg_keys,
+                           (int64_t)grid, best_key_dev);
+        STT_HIP(c, hipGetLastError());
     }
-#undef STT_TM_LAUNCH
+    return STT_OK;
+}
+
+// The free-t_mid wave scorer on map m (format MAPT: kMapPol, kMapF32 or kMapP16).
+template <int MAPT>
+stt_status score_tm_wave(stt_ctx *c, const MapP &m, const GenP &g, const TrkTm *tr, int64_t first, int64_t n, int32_t norm,
+                         float *snr_dev, uint64_t *best_key_dev)
+{
+    auto kern = tr ? (c->hw_trig ? k_score_tm<true, true, MAPT> : k_score_tm<true, false, MAPT>)
+                   : (c->hw_trig ? k_score_tm<false, true, MAPT> : k_score_tm<false, false, MAPT>);
+    ev_record(c, 0);
+    hipLaunchKernelGGL(kern, dim3(wave_grid(n)), dim3(256), 0, c->stream, m, g, tr, (uint64_t)first, n, norm, snr_dev,
+                       best_key_dev);
     STT_HIP(c, hipGetLastError());
     ev_record(c, 1);
     c->used[0] = true;
@@ -1153,13 +1204,19 @@ stt_status stt_score_tm(stt_ctx *c, const stt_map *map, const stt_gen *gen, cons
                       (c->path == 2 || n >= 4096);
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
-    MapP mf;
-    if ((s = fold_polar(c, map, nullptr, mf)) != STT_OK) return s;
-    s = map->dtype == STT_P16
-            ? score_tm_folded<kMapPolH>(c, mf, g, (const TrkTm *)tracks_dev, first, n, norm, snr_dev, best_key_dev,
-                                        slab, lds)
-            : score_tm_folded<kMapPol>(c, mf, g, (const TrkTm *)tracks_dev, first, n, norm, snr_dev, best_key_dev,
-                                       slab, lds);
+    const bool p16 = map->dtype == STT_P16;
+    const TrkTm *tr = (const TrkTm *)tracks_dev;
+    if (!slab && gather_unfolded(map, true, n)) {
+        const MapP m = to_mapp(map);
+        s = p16 ? score_tm_wave<kMapP16>(c, m, g, tr, first, n, norm, snr_dev, best_key_dev)
+                : score_tm_wave<kMapF32>(c, m, g, tr, first, n, norm, snr_dev, best_key_dev);
+    } else {
+        MapP mf;
+        if ((s = fold_polar(c, map, nullptr, mf)) != STT_OK) return s;
+        s = !slab ? score_tm_wave<kMapPol>(c, mf, g, tr, first, n, norm, snr_dev, best_key_dev)
+            : p16 ? score_tm_slabs<kMapPolH>(c, mf, g, first, n, norm, snr_dev, best_key_dev, lds)
+                  : score_tm_slabs<kMapPol>(c, mf, g, first, n, norm, snr_dev, best_key_dev, lds);
+    }
     if (s != STT_OK) return s;
     ev_record(c, 5);
     c->used[2] = true;
@@ -1175,7 +1232,7 @@ stt_status stt_argmax(stt_ctx *c, const float *snr_dev, int64_t n, int64_t first
     if (n == 0) return STT_OK;
     if (!snr_dev || !best_key_dev) return fail(c, STT_EINVAL, "snr_dev and best_key_dev must be non-NULL");
     STT_HIP(c, hipSetDevice(c->device));
-    const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
+    const int64_t blocks = std::min<int64_t>((n + 1023) / 1024, 1024);  // one atomic each
     hipLaunchKernelGGL(k_argmax, dim3((unsigned)blocks), dim3(256), 0, c->stream, snr_dev, n, (uint64_t)first,
                        best_key_dev);
     STT_HIP(c, hipGetLastError());

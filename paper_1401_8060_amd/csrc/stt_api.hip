@@ -42,6 +42,7 @@ struct stt_ctx {
     int lds_bytes = 160 * 1024;  // slab budget per workgroup
     int slab_wg = 1024;          // slab scorer shape: lanes per workgroup
     int slab_tpt = 4;            //                    templates per lane
+    bool auto_shape = true;      // shape and budget by the call's size, until the caller or a tuner sets either
     bool hw_trig = true;         // hardware sine/cosine (measured max error 1.3e-7) or the polynomial
     // Timing: every call takes six events from a pool (start/end of the scoring
     // kernel, of the binning kernels and of the whole call); queries sum them.
@@ -180,7 +181,6 @@ int dma_slab_cols(int lds_bytes, int64_t ldc, int esize = 8)
 {
     return (int)std::min<int64_t>(64, (lds_bytes - 256) / (2 * ldc * esize));
 }
-int dma_slab_cols(const stt_ctx *c, int64_t ldc, int esize = 8) { return dma_slab_cols(c->lds_bytes, ldc, esize); }
 
 stt_status check_map(stt_ctx *c, const stt_map *m)
 {
@@ -354,6 +354,34 @@ int aligned_slab(int cols)
     int sc = 16;
     while (sc > cols) sc >>= 1;
     return sc >= 2 ? sc : 0;
+}
+
+// Shape of a slab scorer launch: lanes per workgroup, templates per lane, LDS budget.
+struct SlabShape {
+    int wg, tpt, lds;
+};
+
+// The shape of a call of n templates (all maps of a batch together) on folded columns of col_bytes,
+// for callers that set none. Two templates per lane run 8 waves per SIMD; what is left is how many
+// templates share a staged slab (fewer stagings) against how many workgroups there are to share the
+// chip. Measured (us, per call):
+//  - up to 400 000 templates there are not enough workgroups for every CU: the smallest, 512 x 2, with
+//    the widest slabs (1000 x 1000, 10^5: 199; 512 x 2 of 80 KB 208, 1024 x 2 221, 1024 x 4 368);
+//  - columns of 12 KB and more: two budgets of 80 KB hold 2-column slabs only, so one workgroup per
+//    CU, of 1024 x 2 while there are few (2000 x 2000, 3 x 10^5: 519, 1024 x 4 746), then 1024 x 4
+//    (10^7: 3021, 1024 x 2 3431, 512 x 4 3322);
+//  - columns of 4 KB and more: 1024 x 2, one per CU up to 1.5 x 10^6 (10^6 on 1000 x 1000: 259; two
+//    per CU 307), then two (10^7: 1311; one per CU 1501; 512 x 4 1327, 1024 x 4 1435; 64 maps x 10^6:
+//    11.9 ms, 1024 x 4 12.1, 512 x 4 12.2);
+//  - narrower columns: 512 x 2 in two per CU, then four (500 x 151, 10^6: 142, four 144; 2 x 10^7:
+//    1336, two 1489, 1024 x 2 1389, 512 x 4 1379).
+SlabShape slab_shape_for(int64_t n, int64_t col_bytes)
+{
+    constexpr int k160 = 160 * 1024, k80 = 80 * 1024, k40 = 40 * 1024;
+    if (n < 400000) return {512, 2, k160};
+    if (col_bytes >= 12 * 1024) return n < 600000 ? SlabShape{1024, 2, k160} : SlabShape{1024, 4, k160};
+    if (col_bytes >= 4 * 1024) return {1024, 2, n < 1500000 ? k160 : k80};
+    return {512, 2, n < 2000000 ? k80 : k40};
 }
 
 // sc > 0: LDS-DMA slabs of sc aligned columns (sc in 2, 4, 8, 16); sc = 0: register staging of
@@ -533,6 +561,16 @@ stt_status bin_templates(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr
     return STT_OK;
 }
 
+// The shape of this call: the context's, or by size while neither shape nor budget has been set and
+// the slabs stream in by DMA (registers stage into one buffer of the whole budget).
+SlabShape call_shape(const stt_ctx *c, int64_t n, int64_t col_bytes)
+{
+    const SlabShape own{c->slab_wg, c->slab_tpt, c->lds_bytes};
+    if (!c->auto_shape || !c->dma) return own;
+    const SlabShape sh = slab_shape_for(n, col_bytes);
+    return aligned_slab(dma_slab_cols(sh.lds, col_bytes, 1)) >= 2 ? sh : own;
+}
+
 // The slab scorer of one call on the folded map m (format MAPT: kMapPol or kMapPolH).
 template <bool EXPL, int MAPT>
 stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n, int32_t norm,
@@ -540,27 +578,28 @@ stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, 
 {
     constexpr int esize = (int)sizeof(elem_t<MAPT>);
     stt_status s;
+    const SlabShape sh = call_shape(c, n, m.ld * esize);
     uint32_t *order = nullptr;
     uint64_t *wg_keys = nullptr;
     if ((s = bin_templates<EXPL>(c, m, g, tr, first, n, fb, order, wg_keys)) != STT_OK) return s;
     const int64_t ldc = m.ld;
-    const int sc = c->dma ? aligned_slab(dma_slab_cols(c, ldc, esize)) : 0;
+    const int sc = c->dma ? aligned_slab(dma_slab_cols(sh.lds, ldc, esize)) : 0;
     if (sc > 0) {
         // aligned slabs of the folded map streamed into LDS with double-buffered DMA
         const size_t shm = 2 * (size_t)esize * (size_t)sc * ldc;
         ev_attach(c, 0, 1);
-        s = launch_slab<MAPT>(c, sc, c->slab_wg, c->slab_tpt, m, g, tr, order, first, n, sc, shm, norm, snr, wg_keys);
+        s = launch_slab<MAPT>(c, sc, sh.wg, sh.tpt, m, g, tr, order, first, n, sc, shm, norm, snr, wg_keys);
     } else {
         // one slab buffer, staged through registers (maps too wide for two DMA slabs)
-        const int S = std::min<int>(std::min<int>(64, (c->lds_bytes - 256) / (esize * m.F)), m.T);
+        const int S = std::min<int>(std::min<int>(64, (sh.lds - 256) / (esize * m.F)), m.T);
         const size_t shm = (size_t)esize * (size_t)S * m.F;
         ev_attach(c, 0, 1);
-        s = launch_slab<MAPT>(c, 0, c->slab_wg, c->slab_tpt, m, g, tr, order, first, n, S, shm, norm, snr, wg_keys);
+        s = launch_slab<MAPT>(c, 0, sh.wg, sh.tpt, m, g, tr, order, first, n, S, shm, norm, snr, wg_keys);
     }
     if (s != STT_OK) return s;
     c->used[0] = true;
     if (best) {
-        const int64_t n_wg = (n + (int64_t)c->slab_wg * c->slab_tpt - 1) / ((int64_t)c->slab_wg * c->slab_tpt);
+        const int64_t n_wg = (n + (int64_t)sh.wg * sh.tpt - 1) / ((int64_t)sh.wg * sh.tpt);
         ev_attach(c, -1, 5);
         launch_ev(c, k_reduce_keys, dim3(1), dim3(1024), 0, (const uint64_t *)wg_keys, n_wg, best);
         STT_HIP(c, hipGetLastError());
@@ -1038,7 +1077,10 @@ stt_status stt_set_path(stt_ctx *c, int32_t path, int32_t lds_bytes)
     if (lds_bytes != 0 && (lds_bytes < 1024 || lds_bytes > 160 * 1024))
         return fail(c, STT_ERANGE, "lds_bytes=%d outside [1024, 163840]", lds_bytes);
     c->path = path;
-    if (lds_bytes) c->lds_bytes = lds_bytes;
+    if (lds_bytes) {
+        c->lds_bytes = lds_bytes;
+        c->auto_shape = false;
+    }
     return STT_OK;
 }
 
@@ -1048,6 +1090,7 @@ stt_status stt_set_slab_shape(stt_ctx *c, int32_t wg, int32_t tpt)
     if (!slab_shape_ok(wg, tpt)) return fail(c, STT_EUNSUPPORTED, "no slab scorer for %d x %d", wg, tpt);
     c->slab_wg = wg;
     c->slab_tpt = tpt;
+    c->auto_shape = false;
     return STT_OK;
 }
 
@@ -1504,12 +1547,12 @@ stt_status launch_batch_t(stt_ctx *c, hipStream_t st, const BatchMap *maps, int 
 }
 
 template <bool HW, int MAPT, int SC>
-stt_status launch_batch_h(stt_ctx *c, hipStream_t st, const BatchMap *maps, int n_maps, const uint32_t *item_start,
+stt_status launch_batch_h(stt_ctx *c, const SlabShape &sh, hipStream_t st, const BatchMap *maps, int n_maps, const uint32_t *item_start,
                           uint32_t total_items, uint32_t *queue, const uint32_t *order, int32_t norm, uint64_t *best,
                           size_t shm)
 {
 #define STT_BATCH_CASE(W, P)                                                                                        \
-    if (c->slab_wg == W && c->slab_tpt == P)                                                                        \
+    if (sh.wg == W && sh.tpt == P)                                                                                  \
         return launch_batch_t<W, P, HW, MAPT, SC>(c, st, maps, n_maps, item_start, total_items, queue, order, norm, \
                                                   best, shm);
     STT_BATCH_CASE(1024, 4)
@@ -1518,7 +1561,7 @@ stt_status launch_batch_h(stt_ctx *c, hipStream_t st, const BatchMap *maps, int 
     STT_BATCH_CASE(1024, 2)
     STT_BATCH_CASE(512, 2)
 #undef STT_BATCH_CASE
-    return fail(c, STT_EUNSUPPORTED, "no batch scorer for %dx%d", c->slab_wg, c->slab_tpt);
+    return fail(c, STT_EUNSUPPORTED, "no batch scorer for %dx%d", sh.wg, sh.tpt);
 }
 
 template <typename T>
@@ -1553,7 +1596,14 @@ stt_status stt_score_batch(stt_ctx *c, const stt_map *maps_host, int32_t n_maps,
     const int esize = fold_esize(dtype);
     std::vector<BatchMap> bm(n_maps);
     std::vector<uint32_t> chunk_start(n_maps + 1), item_start(n_maps + 1), fine_start(n_maps + 1);
-    const int per_item = c->slab_wg * c->slab_tpt;
+    // one shape for the batch, by its total templates and widest column
+    int64_t n_total = 0, widest = 0;
+    for (int i = 0; i < n_maps; ++i) {
+        n_total += std::max<int64_t>(0, n_trk_host[i]);
+        widest = std::max(widest, fold_ld(std::max(1, maps_host[i].F), esize) * esize);
+    }
+    const SlabShape sh = call_shape(c, n_total, widest);
+    const int per_item = sh.wg * sh.tpt;
     uint64_t norder = 0, nchunks = 0, nitems = 0, nfine = 0;
     size_t ncc = 0;     // counts per group and sort chunk, all maps
     int max_groups = 1;  // most groups of any map
@@ -1580,11 +1630,11 @@ stt_status stt_score_batch(stt_ctx *c, const stt_map *maps_host, int32_t n_maps,
         d.wb = bucket_shift(mp->T, n);
         const int nb = ((mp->T - 1) >> d.wb) + 1;
         d.nbins = nb * (nb + 1) / 2;
-        d.S = std::min(std::min<int>(64, (c->lds_bytes - 256) / (esize * mp->F)), mp->T);
+        d.S = std::min(std::min<int>(64, (sh.lds - 256) / (esize * mp->F)), mp->T);
         if (d.S < 1) return fail(c, STT_EUNSUPPORTED, "map %d: F=%d too wide for the LDS slab", i, mp->F);
         {
             const int64_t ldc = fold_ld(mp->F, esize);
-            dma_ok = dma_ok && aligned_slab(dma_slab_cols(c, ldc, esize)) >= 2;
+            dma_ok = dma_ok && aligned_slab(dma_slab_cols(sh.lds, ldc, esize)) >= 2;
             fold_off[i] = fold_px;
             fold_px += (uint64_t)mp->T * (uint64_t)ldc;
             fold_col[i] = fold_cols;
@@ -1626,7 +1676,7 @@ stt_status stt_score_batch(stt_ctx *c, const stt_map *maps_host, int32_t n_maps,
     int sc_all = 16;
     if (dma_ok)
         for (int i = 0; i < n_maps; ++i)
-            sc_all = std::min(sc_all, aligned_slab(dma_slab_cols(c, fold_ld(bm[i].m.F, esize), esize)));
+            sc_all = std::min(sc_all, aligned_slab(dma_slab_cols(sh.lds, fold_ld(bm[i].m.F, esize), esize)));
     for (int i = 0; i < n_maps; ++i) {
         BatchMap &d = bm[i];
         const int64_t ldc = fold_ld(d.m.F, esize);
@@ -1670,9 +1720,7 @@ stt_status stt_score_batch(stt_ctx *c, const stt_map *maps_host, int32_t n_maps,
     key_add(key, norm);
     key_add(key, best_key_per_map_dev);
     key_add(key, c->scratch);
-    key_add(key, c->slab_wg);
-    key_add(key, c->slab_tpt);
-    key_add(key, c->lds_bytes);
+    key_add(key, sh);
     key_add(key, c->hw_trig);
     key_add(key, dma_ok);
     key_add(key, sc_all);
@@ -1749,9 +1797,9 @@ stt_status stt_score_batch(stt_ctx *c, const stt_map *maps_host, int32_t n_maps,
             const uint32_t ni = (uint32_t)nitems;
             const int sc = dma_ok ? sc_all : 0;
 #define STT_BATCH_SC(MT, SCV)                                                                                  \
-    r = c->hw_trig ? launch_batch_h<true, MT, SCV>(c, st, dmaps, n_maps, ditem, ni, queue, order, norm,        \
+    r = c->hw_trig ? launch_batch_h<true, MT, SCV>(c, sh, st, dmaps, n_maps, ditem, ni, queue, order, norm,        \
                                                    best_key_per_map_dev, shm)                                 \
-                   : launch_batch_h<false, MT, SCV>(c, st, dmaps, n_maps, ditem, ni, queue, order, norm,       \
+                   : launch_batch_h<false, MT, SCV>(c, sh, st, dmaps, n_maps, ditem, ni, queue, order, norm,       \
                                                     best_key_per_map_dev, shm)
 #define STT_BATCH_MT(MT)                                                                                       \
     switch (sc) {                                                                                              \
@@ -2007,7 +2055,8 @@ std::string tune_key_batch(const stt_ctx *c, int F, int dtype, int T, int n_maps
 stt_status tune_search(stt_ctx *c, int F, int reps, const std::function<stt_status()> &call, TuneChoice &best)
 {
     const int old_path = c->path, old_wg = c->slab_wg, old_tpt = c->slab_tpt, old_lds = c->lds_bytes;
-    const bool old_timing = c->timing, old_graph = c->use_graph;
+    const bool old_timing = c->timing, old_graph = c->use_graph, old_auto = c->auto_shape;
+    c->auto_shape = false;
     std::vector<Rec> saved;
     saved.swap(c->recs);
     const size_t saved_next = c->next;
@@ -2045,6 +2094,7 @@ stt_status tune_search(stt_ctx *c, int F, int reps, const std::function<stt_stat
     c->lds_bytes = old_lds;
     c->timing = old_timing;
     c->use_graph = old_graph;
+    c->auto_shape = old_auto;
     c->recs.swap(saved);
     c->next = saved_next;
     if (s != STT_OK) return s;
@@ -2059,6 +2109,7 @@ stt_status apply_choice(stt_ctx *c, const std::string &key, const TuneChoice &be
     c->slab_wg = best.wg;
     c->slab_tpt = best.tpt;
     c->lds_bytes = best.lds;
+    c->auto_shape = false;
     if (choice_out) {
         choice_out[0] = best.wg;
         choice_out[1] = best.tpt;

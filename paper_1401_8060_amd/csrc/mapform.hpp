@@ -18,9 +18,10 @@
 
 namespace stt {
 
-constexpr int kFftThreads = 256;
+constexpr int kFftThreads = 256;   // at most; a column of N points uses N / 8
 constexpr int kMaxFftM = 8192;     // samples per column; the complex FFT has M/2 points in LDS
-constexpr int kSlidesPerLaunch = 16;
+constexpr int kSlidesPerLaunch = 64;  // 20 bytes each of the 4 KB of kernel arguments
+constexpr int kPsdCols = 4;        // columns per lane of k_psd
 
 struct SlideArgs {
     float2 *Y[kSlidesPerLaunch];
@@ -29,8 +30,75 @@ struct SlideArgs {
     int32_t n;
 };
 
+// LDS word of FFT element i. Passes touch elements 2^s apart from lanes 8 or 64 elements apart; the
+// pad spreads both over the banks.
+__host__ __device__ __forceinline__ constexpr int fft_slot(int i) { return i + (i >> 5) + ((i >> 6) << 3); }
+
+// Stages s .. s+G-1 of the radix-2 decimation in time on the 2^G elements v[j] at i0 + j 2^s, low =
+// i0 mod 2^s: stage s+q joins blocks of 2^(s+q) elements, e^{-2 pi i p / 2^(s+q+1)} = tw[p M / 2^(s+q+1)].
+template <int G>
+__device__ __forceinline__ void fft_stages(float2 *v, int s, int low, int M, const float2 *__restrict__ tw)
+{
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+        const int tstep = M >> (s + q + 1);
+#pragma unroll
+        for (int p = 0; p < (1 << q); ++p) {
+            const float2 w = tw[(low + (p << s)) * tstep];
+#pragma unroll
+            for (int j = p; j < (1 << G); j += 2 << q) {
+                const float2 a = v[j], c = v[j + (1 << q)];
+                const float cr = w.x * c.x - w.y * c.y, ci = w.x * c.y + w.y * c.x;
+                v[j] = make_float2(a.x + cr, a.y + ci);
+                v[j + (1 << q)] = make_float2(a.x - cr, a.y - ci);
+            }
+        }
+    }
+}
+
+// First pass: 2^G windowed samples straight from the strain. Element r of the bit-reversed order
+// holds sample pair bitrev(r); lane w takes r = 2^G bitrev(w) + j, sample pairs w + bitrev(j) N/2^G.
+template <int G>
+__device__ __forceinline__ void fft_load_pass(float2 *z, const float2 *__restrict__ seg, const float2 *__restrict__ win2,
+                                              int M, int lg, const float2 *__restrict__ tw)
+{
+    const int items = 1 << (lg - G);
+    for (int w = threadIdx.x; w < items; w += blockDim.x) {
+        float2 v[1 << G];
+#pragma unroll
+        for (int j = 0; j < (1 << G); ++j) {
+            const int i = w + (int)(__builtin_bitreverse32((unsigned)j) >> (32 - G)) * items;
+            const float2 x = seg[i], h = win2[i];
+            v[j] = make_float2(x.x * h.x, x.y * h.y);
+        }
+        fft_stages<G>(v, 0, 0, M, tw);
+        const int r = lg > G ? (int)(__builtin_bitreverse32((unsigned)w) >> (32 - (lg - G))) << G : 0;
+#pragma unroll
+        for (int j = 0; j < (1 << G); ++j) z[fft_slot(r + j)] = v[j];
+    }
+}
+
+template <int G>
+__device__ __forceinline__ void fft_pass(float2 *z, int s, int M, int lg, const float2 *__restrict__ tw)
+{
+    __syncthreads();
+    for (int w = threadIdx.x; w < 1 << (lg - G); w += blockDim.x) {
+        const int low = w & ((1 << s) - 1);
+        const int i0 = ((w >> s) << (s + G)) + low;
+        float2 v[1 << G];
+#pragma unroll
+        for (int j = 0; j < (1 << G); ++j) v[j] = z[fft_slot(i0 + (j << s))];
+        fft_stages<G>(v, s, low, M, tw);
+#pragma unroll
+        for (int j = 0; j < (1 << G); ++j) z[fft_slot(i0 + (j << s))] = v[j];
+    }
+}
+
 // x: strain (8-byte aligned); tab: M/2 twiddles (float2) followed by M window values (float);
-// spec: [T][F] complex64. Grid: T workgroups of kFftThreads lanes, N = M/2 float2 of LDS.
+// spec: [T][F] complex64. Grid: T workgroups, fft_slot(N) float2 of LDS, N = M/2 = 2^lg >= 4.
+// Bound by latency: a stage at a time through LDS was 11 barriers and a twiddle gather in front of
+// each at M = 4096. Three stages at a time stay in registers (the same butterflies in the same
+// order, so the same bits), and the first three take the samples straight from memory.
 __global__ __launch_bounds__(kFftThreads) void k_col_fft(const float *__restrict__ x, int M, int lg, int k_lo, int F,
                                                          float dt, const float2 *__restrict__ tab,
                                                          float2 *__restrict__ spec)
@@ -40,35 +108,25 @@ __global__ __launch_bounds__(kFftThreads) void k_col_fft(const float *__restrict
     const float2 *tw = tab;
     const float2 *win2 = reinterpret_cast<const float2 *>(tab + N);  // window pairs (w[2i], w[2i+1])
     const int t = blockIdx.x;
+    // even/odd sample pairs as one complex sequence
     const float2 *seg = reinterpret_cast<const float2 *>(x + (int64_t)t * N);
-    // even/odd sample pairs as one complex sequence, stored in bit-reversed order
-    for (int i = threadIdx.x; i < N; i += kFftThreads) {
-        const float2 v = seg[i], w = win2[i];
-        const unsigned r = __builtin_bitreverse32((unsigned)i) >> (32 - lg);
-        z[r] = make_float2(v.x * w.x, v.y * w.y);
+    int s;
+    if (lg >= 3) {
+        fft_load_pass<3>(z, seg, win2, M, lg, tw);
+        s = 3;
+    } else {
+        fft_load_pass<2>(z, seg, win2, M, lg, tw);
+        s = 2;
     }
+    for (; s + 3 <= lg; s += 3) fft_pass<3>(z, s, M, lg, tw);
+    if (lg - s == 2) fft_pass<2>(z, s, M, lg, tw);
+    else if (lg - s == 1) fft_pass<1>(z, s, M, lg, tw);
     __syncthreads();
-    // radix-2 decimation in time: stage s joins blocks of 2^s into blocks of 2^(s+1)
-    for (int s = 0; s < lg; ++s) {
-        const int half = 1 << s;
-        const int tstep = M >> (s + 1);  // e^{-2 pi i p / 2^(s+1)} = tw[p * M / 2^(s+1)]
-        for (int b = threadIdx.x; b < (N >> 1); b += kFftThreads) {
-            const int p = b & (half - 1);
-            const int i0 = ((b >> s) << (s + 1)) + p;
-            const int i1 = i0 + half;
-            const float2 w = tw[p * tstep];
-            const float2 a = z[i0], c = z[i1];
-            const float cr = w.x * c.x - w.y * c.y, ci = w.x * c.y + w.y * c.x;
-            z[i0] = make_float2(a.x + cr, a.y + ci);
-            z[i1] = make_float2(a.x - cr, a.y - ci);
-        }
-        __syncthreads();
-    }
     // X[k] = E[k] + e^{-2 pi i k / M} O[k] with E = (Z[k] + conj Z[N-k]) / 2 (even samples) and
     // O = (Z[k] - conj Z[N-k]) / 2i (odd samples); only the kept bins k_lo .. k_lo+F-1 (< N)
-    for (int f = threadIdx.x; f < F; f += kFftThreads) {
+    for (int f = threadIdx.x; f < F; f += blockDim.x) {
         const int k = k_lo + f;
-        const float2 a = z[k], b = z[(N - k) & (N - 1)];
+        const float2 a = z[fft_slot(k)], b = z[fft_slot((N - k) & (N - 1))];
         const float er = 0.5f * (a.x + b.x), ei = 0.5f * (a.y - b.y);
         const float orr = 0.5f * (a.y + b.y), oi = -0.5f * (a.x - b.x);
         const float2 w = tw[k];
@@ -78,64 +136,77 @@ __global__ __launch_bounds__(kFftThreads) void k_col_fft(const float *__restrict
 }
 
 // P'(t; f) = scale * mean |spec(t', f)|^2 over 2 <= |t' - t| <= nb + 1 inside [0, T).
-// Grid: (ceil(F / 256), T); every column has a neighbour (T >= 4, checked by the host).
+// Grid: (ceil(F / 256), ceil(T / kPsdCols)); every column has a neighbour (T >= 4, checked by the
+// host). A lane sums kPsdCols columns, each neighbour read once for all of them (3.5 reads per column
+// instead of 8 at nb = 4); every sum runs over t' in ascending order.
 __global__ __launch_bounds__(256) void k_psd(const float2 *__restrict__ spec, int T, int F, int nb, float scale,
                                              float *__restrict__ psd)
 {
     const int f = blockIdx.x * 256 + threadIdx.x;
-    const int t = blockIdx.y;
+    const int t0 = blockIdx.y * kPsdCols;
     if (f >= F) return;
-    float acc = 0.f;
-    int cnt = 0;
-    for (int u = t - nb - 1; u <= t + nb + 1; ++u) {
-        if (u < 0 || u >= T || (u - t <= 1 && t - u <= 1)) continue;
+    float acc[kPsdCols] = {};
+    const int lo = max(t0 - nb - 1, 0), hi = min(t0 + kPsdCols + nb, T - 1);
+#pragma unroll 4
+    for (int u = lo; u <= hi; ++u) {
         const float2 v = spec[(int64_t)u * F + f];
-        acc += v.x * v.x + v.y * v.y;
-        ++cnt;
+        const float q = v.x * v.x + v.y * v.y;
+#pragma unroll
+        for (int j = 0; j < kPsdCols; ++j) {
+            const int d = u > t0 + j ? u - t0 - j : t0 + j - u;
+            if (d >= 2 && d <= nb + 1) acc[j] += q;
+        }
     }
-    psd[(int64_t)t * F + f] = scale * acc / (float)cnt;
+#pragma unroll
+    for (int j = 0; j < kPsdCols; ++j) {
+        const int t = t0 + j;
+        if (t >= T) break;
+        const int cnt = max(0, min(nb, t - 1)) + max(0, min(nb, T - 2 - t));
+        psd[(int64_t)t * F + f] = scale * acc[j] / (float)cnt;
+    }
 }
 
-// One launch writes up to kSlidesPerLaunch slide maps. Lanes run along frequency, P bins each
-// (P = 2 when F and ld are even and the buffers 16-byte aligned: one 16-byte and one 8-byte store
-// per lane per slide), so every store is a coalesced row segment. Workgroups go round-robin to the
-// 8 XCDs; the remap gives each XCD a contiguous run of columns t, so the J columns t + shift that
-// its slides read stay in its own L2 instead of crossing to the MALL once per slide.
-// Grid: 1-D, ceil(nbx * T / 8) * 8 workgroups of 256 lanes, nbx = ceil(F / (256 P)).
+// One launch writes up to kSlidesPerLaunch slide maps, one after the other: a workgroup takes 256 P
+// consecutive bins of one slide (rows of F bins end to end; P = 2 when F and ld are even and the
+// buffers 16-byte aligned: one 16-byte and one 8-byte store per lane), so that the workgroups in
+// flight write a map or two front to back. Stores past the caches in that order reach the rate of a
+// fill: 256 maps of 1000 x 1000 in 448 us, 6.9 TB/s of the card's 6.9. A workgroup that wrote its
+// bins to 16 maps in turn scattered the stores over 16 maps at once (915 us; past the caches 765);
+// two slides per workgroup take 511 us, stores through the caches 723. Workgroups go round-robin to
+// the 8 XCDs; the remap gives each XCD one contiguous run of bins of every slide, so its I columns,
+// and for neighbouring shifts its J columns, stay in its own L2 (shifts in random order: 677 us).
+// Grid: 1-D, 8 * ceil(nchunk / 8) * a.n workgroups of 256 lanes, nchunk = ceil(T F / (256 P)).
 template <int P>
 __global__ __launch_bounds__(256) void k_form_maps(const float2 *__restrict__ si, const float *__restrict__ pi,
                                                    const float2 *__restrict__ sj, const float *__restrict__ pj,
                                                    int T, int F, float scale, int64_t ld, SlideArgs a)
 {
-    const int nbx = (F + 256 * P - 1) / (256 * P);
-    const int64_t nblk = (int64_t)nbx * T;
-    const int64_t per = (nblk + 7) / 8;
-    const int64_t L = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-    if (L >= nblk) return;
-    const int t = (int)(L / nbx);
-    const int f = P * ((int)(L % nbx) * 256 + (int)threadIdx.x);
-    if (f >= F) return;
+    const uint32_t n = (uint32_t)T * (uint32_t)F;  // < 2^29 (T < 2^16, F <= kMaxFftM / 2)
+    const uint32_t nchunk = (n + 256 * P - 1) / (256 * P);
+    const uint32_t per = (nchunk + 7) / 8;
+    const uint32_t b = blockIdx.x / 8, k = b / per;
+    const uint32_t L = (blockIdx.x % 8) * per + (b - k * per);
+    if (L >= nchunk) return;
+    const uint32_t i = P * (L * 256 + threadIdx.x);
+    if (i >= n) return;
+    uint32_t j = i + (uint32_t)a.shift[k] * (uint32_t)F;  // column t + shift, modulo T
+    if (j >= n) j -= n;
     typedef float fv __attribute__((ext_vector_type(2 * P)));  // P complex values
     typedef float pv __attribute__((ext_vector_type(P)));      // P powers
-    const fv u = *reinterpret_cast<const fv *>(si + (int64_t)t * F + f);
-    const pv pu = *reinterpret_cast<const pv *>(pi + (int64_t)t * F + f);
-    for (int k = 0; k < a.n; ++k) {
-        int tj = t + a.shift[k];
-        if (tj >= T) tj -= T;
-        const fv v = *reinterpret_cast<const fv *>(sj + (int64_t)tj * F + f);
-        const pv pq = *reinterpret_cast<const pv *>(pj + (int64_t)tj * F + f);
-        fv y;
-        pv sg;
+    const fv u = *reinterpret_cast<const fv *>(si + i), v = *reinterpret_cast<const fv *>(sj + j);
+    const pv pu = *reinterpret_cast<const pv *>(pi + i), pq = *reinterpret_cast<const pv *>(pj + j);
+    fv y;
+    pv sg;
 #pragma unroll
-        for (int q = 0; q < P; ++q) {
-            const float ur = u[2 * q], ui = u[2 * q + 1], vr = v[2 * q], vi = v[2 * q + 1];
-            y[2 * q] = scale * (ur * vr + ui * vi);
-            y[2 * q + 1] = scale * (ur * vi - ui * vr);
-            sg[q] = sqrtf(0.5f * pu[q] * pq[q]);
-        }
-        *reinterpret_cast<fv *>(a.Y[k] + (int64_t)t * ld + f) = y;
-        *reinterpret_cast<pv *>(a.sigma[k] + (int64_t)t * ld + f) = sg;
+    for (int q = 0; q < P; ++q) {
+        const float ur = u[2 * q], ui = u[2 * q + 1], vr = v[2 * q], vi = v[2 * q + 1];
+        y[2 * q] = scale * (ur * vr + ui * vi);
+        y[2 * q + 1] = scale * (ur * vi - ui * vr);
+        sg[q] = sqrtf(0.5f * pu[q] * pq[q]);
     }
+    const int64_t o = ld == F ? (int64_t)i : (int64_t)(i / (uint32_t)F) * (ld - F) + i;
+    __builtin_nontemporal_store(y, reinterpret_cast<fv *>(a.Y[k] + o));
+    __builtin_nontemporal_store(sg, reinterpret_cast<pv *>(a.sigma[k] + o));
 }
 
 }  // namespace stt

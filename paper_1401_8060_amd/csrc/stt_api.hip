@@ -1456,11 +1456,12 @@ stt_status stt_spectra(stt_ctx *c, const stt_spectro *p, const float *strain_dev
     int lg = 0;
     while ((1 << lg) < N) ++lg;
     ev_record(c, 4);
-    hipLaunchKernelGGL(k_col_fft, dim3(T), dim3(kFftThreads), sizeof(float2) * N, c->stream, strain_dev, p->M, lg,
+    const int fft_wg = std::min(kFftThreads, std::max(64, N / 8));
+    hipLaunchKernelGGL(k_col_fft, dim3(T), dim3(fft_wg), sizeof(float2) * fft_slot(N), c->stream, strain_dev, p->M, lg,
                        p->k_lo, p->F, (float)(1.0 / p->fs), (const float2 *)c->fft_tab, (float2 *)spec_dev);
     STT_HIP(c, hipGetLastError());
-    hipLaunchKernelGGL(k_psd, dim3((p->F + 255) / 256, T), dim3(256), 0, c->stream, (const float2 *)spec_dev, T, p->F,
-                       p->nb, cross_scale(p), psd_dev);
+    hipLaunchKernelGGL(k_psd, dim3((p->F + 255) / 256, (T + kPsdCols - 1) / kPsdCols), dim3(256), 0, c->stream,
+                       (const float2 *)spec_dev, T, p->F, std::min(p->nb, T), cross_scale(p), psd_dev);
     STT_HIP(c, hipGetLastError());
     ev_record(c, 5);
     c->used[2] = true;
@@ -1493,21 +1494,24 @@ stt_status stt_form_maps(stt_ctx *c, const stt_spectro *p, int32_t T, const floa
     for (int k = 0; k < n_slides && pair; ++k)
         pair = !((uintptr_t)Y_dev[k] & 15) && !((uintptr_t)sigma_dev[k] & 7);
     const int per_lane = pair ? 2 : 1;
-    const int64_t nblk = (int64_t)((p->F + 256 * per_lane - 1) / (256 * per_lane)) * T;
-    const dim3 grid((unsigned)((nblk + 7) / 8 * 8));
+    const int64_t nchunk = ((int64_t)T * p->F + 256 * per_lane - 1) / (256 * per_lane);
     STT_HIP(c, hipSetDevice(c->device));
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
     ev_record(c, 0);
-    for (int k0 = 0; k0 < n_slides; k0 += kSlidesPerLaunch) {
+    // a launch holds below 2^32 lanes: at least 15 slides of the largest map
+    const int64_t slide_wgs = 8 * ((nchunk + 7) / 8);
+    const int per_launch = (int)std::min<int64_t>(kSlidesPerLaunch, (((int64_t)1 << 24) - 1) / slide_wgs);
+    for (int k0 = 0; k0 < n_slides; k0 += per_launch) {
         SlideArgs a{};
-        a.n = std::min(kSlidesPerLaunch, n_slides - k0);
+        a.n = std::min(per_launch, n_slides - k0);
         for (int k = 0; k < a.n; ++k) {
             a.Y[k] = (float2 *)Y_dev[k0 + k];
             a.sigma[k] = sigma_dev[k0 + k];
             const int64_t sh = shifts[k0 + k] % T;
             a.shift[k] = (int32_t)(sh < 0 ? sh + T : sh);
         }
+        const dim3 grid((unsigned)(slide_wgs * a.n));
         if (pair)
             hipLaunchKernelGGL(k_form_maps<2>, grid, dim3(256), 0, c->stream, (const float2 *)spec_i_dev, psd_i_dev,
                                (const float2 *)spec_j_dev, psd_j_dev, T, p->F, cross_scale(p), ld, a);

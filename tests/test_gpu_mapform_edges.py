@@ -1,0 +1,85 @@
+"""Map formation at the edges of its kernels: every number of FFT passes, columns that do not fill
+the power sums' groups, and slides written one after the other by flat bins (odd band widths, padded
+rows, misaligned buffers, ragged launches).
+
+Tolerances from the FP32 arithmetic: spectra 1e-5 of their rms (they err by less than 1e-6 of it,
+d); P' = scale mean |s|^2 by its own roundings, 1e-5 relative, plus what d moves it by,
+2 d sqrt(scale P'); sigma 1e-5 relative; Y 4 roundings of products of spectra: 1e-6 of |s_I| |s_J|.
+"""
+from __future__ import annotations
+
+import sys
+
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def stt():
+    import paper_1401_8060_amd.stt as stt
+    return stt
+
+
+@pytest.fixture(scope="module")
+def ctx(stt):
+    c = stt.Context(0)
+    yield c
+    c.close()
+
+
+def _dev(x):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+@pytest.mark.parametrize("lg_M", range(3, 14))
+def test_spectra_every_fft_length(stt, ctx, lg_M):
+    from oracle import mapform
+    M = 1 << lg_M
+    T, nb = 5 + lg_M % 4, 1 + lg_M % 9  # T mod 4 takes every value; nb beyond T too
+    print("spectra", M, T, nb, flush=True, file=sys.stderr)
+    x = synth.white_strain((T + 1) * M // 2, seed=lg_M)
+    spec, psd = ctx.spectra(_dev(x), stt.Spectro(float(M), M, 0, M // 2, nb), T)
+    want = mapform.column_spectra(x, float(M), M, T, 0, M // 2)
+    rms = np.sqrt(np.mean(np.abs(want) ** 2))
+    assert np.abs(spec.cpu().numpy() - want).max() <= 1e-5 * rms
+    pw = mapform.psd(want, float(M), M, nb)
+    scale = 2.0 / 0.375  # fs = M: 1 s columns
+    assert (np.abs(psd.cpu().numpy() - pw) <= 1e-5 * pw + 2e-6 * rms * np.sqrt(scale * pw)).all()
+
+
+@pytest.mark.parametrize("T,F,pad,off,ns", [(4, 1, 0, 0, 3), (7, 29, 0, 0, 65), (8, 30, 0, 0, 64), (8, 30, 2, 0, 9),
+                                            (8, 30, 5, 0, 9), (64, 64, 0, 1, 5), (33, 62, 0, 0, 130)])
+def test_slides_by_flat_bins(stt, ctx, T, F, pad, off, ns):
+    """Y = scale conj(s_I) s_J(t + shift), sigma = sqrt(P_I P_J(t + shift) / 2); nothing outside the rows."""
+    import torch
+    print("slides", T, F, pad, off, ns, flush=True, file=sys.stderr)
+    rng = np.random.default_rng(T * F)
+    M, ld = 256, F + pad
+    p = stt.Spectro(256.0, M, 3, F, 2)
+    si, sj = (rng.standard_normal((T, F, 2)).astype(np.float32).view(np.complex64)[..., 0] for _ in range(2))
+    pi, pj = (rng.random((T, F)).astype(np.float32) + 0.5 for _ in range(2))
+    shifts = [int(s) for s in rng.integers(-2 * T, 2 * T, ns)]
+    canary = 12345.0
+    Ys = [torch.full((T * ld + off, 2), canary, device="cuda") for _ in range(ns)]
+    sg = [torch.full((T * ld + off,), canary, device="cuda") for _ in range(ns)]
+    maps = []
+    for Y, s in zip(Ys, sg):
+        Yv = torch.view_as_complex(Y[off:].reshape(T, ld, 2))[:, :F]
+        maps.append(stt.Map(Yv, s[off:].reshape(T, ld)[:, :F], 16 * 3, 16))
+    ctx.form_maps(p, _dev(si), _dev(pi), _dev(sj), _dev(pj), shifts, out=maps)
+    scale = 2.0 / (M / 256.0 * 0.375)
+    for k, sh in enumerate(shifts):
+        idx = (np.arange(T) + sh) % T
+        y, s = Ys[k][off:].cpu().numpy().reshape(T, ld, 2), sg[k][off:].cpu().numpy().reshape(T, ld)
+        want = scale * np.conj(si.astype(complex)) * sj[idx]
+        got = y[:, :F, 0] + 1j * y[:, :F, 1]
+        assert (np.abs(got - want) <= 1e-6 * scale * np.abs(si) * np.abs(sj[idx])).all()
+        ws = np.sqrt(0.5 * pi.astype(float) * pj[idx])
+        assert (np.abs(s[:, :F] - ws) <= 1e-5 * ws).all()
+        assert (y[:, F:] == canary).all() and (s[:, F:] == canary).all()
+        assert bool((Ys[k][:off] == canary).all()) and bool((sg[k][:off] == canary).all())

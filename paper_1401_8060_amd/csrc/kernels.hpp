@@ -2114,7 +2114,8 @@ __global__ __launch_bounds__(WG, (kSlabWavesPerSimd<TPT, SC>)) void k_score_batc
 // FP64; its argument atan2 / (2 pi) to the nearest 2^-16 turn (ties to even),
 // modulo one turn. Word = argument | binary16 bits << 16. k_absmax_p finds the
 // largest magnitude first (its FP64 bits: non-negative doubles order as
-// integers).
+// integers), one atomic per workgroup of at most 1024: atomics on one address
+// follow one another, 11 ns each, and one per wave of 2048 workgroups was 100 us.
 
 __device__ __forceinline__ double p_mag64(float x, float y)
 {
@@ -2144,15 +2145,21 @@ __global__ __launch_bounds__(256) void k_absmax_p(MapP m, unsigned long long *am
     double mx = 0.0;
     const int64_t n = (int64_t)m.T * m.F;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-        const int64_t t = i / m.F, r = i - t * m.F;
+        const int64_t t = n >> 32 ? i / m.F : (int64_t)((uint32_t)i / (uint32_t)m.F), r = i - t * m.F;
         const int64_t e = t * m.ld + r;
         const float2 y = m.Y[e];
         const float sg = m.sig[e];
         mx = fmax(mx, p_mag64(y.x / sg, y.y / sg));
     }
+    __shared__ double red[4];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-    if ((threadIdx.x & 63) == 0) atomicMax(amax_bits, (unsigned long long)__double_as_longlong(mx));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+        if (mx > 0.0) atomicMax(amax_bits, (unsigned long long)__double_as_longlong(mx));
+    }
 }
 
 __global__ __launch_bounds__(256) void k_pack_p16(MapP m, double inv_scale, uint32_t *out, int64_t out_ld)
@@ -2311,47 +2318,54 @@ __global__ __launch_bounds__(256) void k_topk_hist(SRC src, int64_t n, uint64_t 
         if (h[i]) atomicAdd(&st->hist[pass][i], h[i]);
 }
 
-// The keys at or above the final prefix into cand (at most kTopkCand), one cursor atomic per
-// workgroup and batch of elements that holds any.
+// The keys at or above the final prefix into cand (at most kTopkCand), by a list in LDS and one
+// cursor atomic per workgroup; keys beyond the list take a cursor atomic each.
+constexpr int kTopkList = 1024;
+
 template <typename SRC>
 __global__ __launch_bounds__(256) void k_topk_gather(SRC src, int64_t n, uint64_t first, TopkState *st, uint64_t *cand)
 {
+    __shared__ uint64_t list[kTopkList];
     __shared__ uint32_t cnt, base;
+    if (threadIdx.x == 0) cnt = 0;
     const TopkSel s = topk_resolve(st, kTopkPasses);
+    __syncthreads();
     const uint64_t thr = s.prefix >> s.shift;
     const int64_t stride = (int64_t)gridDim.x * 256;
-    for (int64_t b0 = (int64_t)blockIdx.x * 256; b0 < n; b0 += 8 * stride) {  // uniform over the workgroup
-        uint64_t k[8];
-        uint32_t at[8];
-        if (threadIdx.x == 0) cnt = 0;
-        __syncthreads();
+    for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += 8 * stride) {
+        float z[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) z[q] = i0 + q * stride < n ? src(i0 + q * stride) : 0.0f;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int64_t i = b0 + q * stride + threadIdx.x;
-            k[q] = i < n ? key_encode(src(i), (uint32_t)(first + (uint64_t)i)) : 0;  // a real key is > 0
+            const int64_t i = i0 + q * stride;
+            if (i >= n) break;
+            const uint64_t k = key_encode(z[q], (uint32_t)(first + (uint64_t)i));
+            if (k >> s.shift < thr) continue;
+            const uint32_t at = atomicAdd(&cnt, 1u);
+            if (at < (uint32_t)kTopkList) {
+                list[at] = k;
+            } else {
+                const uint32_t o = atomicAdd(&st->count, 1u);
+                if (o < (uint32_t)kTopkCand) cand[o] = k;  // the bound is a guard
+            }
         }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const bool in = k[q] && k[q] >> s.shift >= thr;
-            if (!in) k[q] = 0;
-            else at[q] = atomicAdd(&cnt, 1u);
-        }
-        __syncthreads();
-        if (threadIdx.x == 0 && cnt) base = atomicAdd(&st->count, cnt);
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (k[q] && base + at[q] < (uint32_t)kTopkCand) cand[base + at[q]] = k[q];  // the bound is a guard
     }
+    __syncthreads();
+    const uint32_t m = min(cnt, (uint32_t)kTopkList);
+    if (threadIdx.x == 0 && m) base = atomicAdd(&st->count, m);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < m; i += 256)
+        if (base + i < (uint32_t)kTopkCand) cand[base + i] = list[i];
 }
 
-// Rank of each candidate (64 per workgroup, a lane each; the four waves compare with a quarter of
+// Rank of each candidate (64 per workgroup, a lane each; the 16 waves compare with a sixteenth of
 // the candidates each): ranks below K are the answer, in order. last_only: val holds one score,
 // that of rank K - 1.
-__global__ __launch_bounds__(256) void k_topk_rank(const TopkState *st, const uint64_t *cand, int K, int last_only,
-                                                   int64_t *idx, float *val)
+__global__ __launch_bounds__(1024) void k_topk_rank(const TopkState *st, const uint64_t *cand, int K, int last_only,
+                                                    int64_t *idx, float *val)
 {
-    constexpr int kTile = 1024;
+    constexpr int kTile = 4096;
     __shared__ uint64_t tile[kTile];
     __shared__ uint32_t rank[64];
     const int C = (int)min(st->count, (uint32_t)kTopkCand);
@@ -2362,12 +2376,13 @@ __global__ __launch_bounds__(256) void k_topk_rank(const TopkState *st, const ui
     if (threadIdx.x < 64) rank[threadIdx.x] = 0;
     uint32_t r = 0;
     for (int t0 = 0; t0 < C; t0 += kTile) {
+        const int tn = min(kTile, C - t0), per = (tn + 15) / 16;
         __syncthreads();
-        for (int i = threadIdx.x; i < kTile; i += 256) tile[i] = t0 + i < C ? cand[t0 + i] : 0;
+        for (int i = threadIdx.x; i < tn; i += 1024) tile[i] = cand[t0 + i];
         __syncthreads();
-        const int q0 = wave * (kTile / 4), q1 = min(q0 + kTile / 4, C - t0);
+        const int q1 = min(wave * per + per, tn);
 #pragma unroll 8
-        for (int q = q0; q < q1; ++q) r += tile[q] > k;  // one LDS broadcast per key
+        for (int q = wave * per; q < q1; ++q) r += tile[q] > k;  // one LDS broadcast per key
     }
     atomicAdd(&rank[lane], r);
     __syncthreads();
@@ -2435,17 +2450,56 @@ __global__ __launch_bounds__(256) void k_rescore_f64(MapP m, GenP g, const Trk *
 // of its dtau-derivative; z~ = K^-1/2 sum. One wave per template, lanes over
 // samples; sums in FP64, reduced in a fixed order (deterministic).
 
-template <int MAPT>
-__device__ __forceinline__ void smooth_node(const MapP &m, int64_t t, int64_t r, double dtau_s, float &g, float &gd)
+// cos and sin of a row's phase and its frequency, shared by the row's nodes.
+struct RowPhase {
+    float c, s, w;  // w = -2 pi f
+};
+
+__device__ __forceinline__ RowPhase row_phase(const MapP &m, int r, double dtau_s)
 {
-    const float2 p = load_p<MAPT>(m, t * m.ld + r);
-    const double f_hz = (double)(m.fq4_lo + r * m.dfq4) * 0.0625;
+    const double f_hz = (double)(m.fq4_lo + (int64_t)r * m.dfq4) * 0.0625;
     double turns = f_hz * dtau_s;
     turns -= floor(turns);
     const float x = (float)turns;
-    const float c = __builtin_amdgcn_cosf(x), s = __builtin_amdgcn_sinf(x);
-    g = c * p.x - s * p.y;
-    gd = -6.283185307179586f * (float)f_hz * (s * p.x + c * p.y);
+    return {__builtin_amdgcn_cosf(x), __builtin_amdgcn_sinf(x), -6.283185307179586f * (float)f_hz};
+}
+
+__device__ __forceinline__ void smooth_node(float2 p, const RowPhase &h, float &g, float &gd)
+{
+    g = h.c * p.x - h.s * p.y;
+    gd = h.w * (h.s * p.x + h.c * p.y);
+}
+
+// p of two neighbouring rows of one column.
+template <int MAPT>
+__device__ __forceinline__ void load_p2(const MapP &m, int64_t e, float2 &p0, float2 &p1)
+{
+    if constexpr (MAPT == kMapPF) {
+        typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
+        const f4 v = *reinterpret_cast<const f4 *>(m.Y + e);
+        p0 = make_float2(v.x, v.y);
+        p1 = make_float2(v.z, v.w);
+    } else {
+        p0 = load_p<MAPT>(m, e);
+        p1 = load_p<MAPT>(m, e + 1);
+    }
+}
+
+// Sums of 8 values over the wave, value q in the lanes with lane % 8 == q on return. The first three
+// exchanges halve what each lane carries (10 exchanges for all 8; value by value they were 48).
+__device__ __forceinline__ double wave_sum8(const double (&x)[8])
+{
+    const int lane = threadIdx.x & 63;
+    double y[4], z[2];
+    const bool h4 = lane & 4, h2 = lane & 2, h1 = lane & 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) y[q] = (h4 ? x[q + 4] : x[q]) + __shfl_xor(h4 ? x[q] : x[q + 4], 4);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) z[q] = (h2 ? y[q + 2] : y[q]) + __shfl_xor(h2 ? y[q] : y[q + 2], 2);
+    double v = (h1 ? z[1] : z[0]) + __shfl_xor(h1 ? z[0] : z[1], 1);
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) v += __shfl_xor(v, off);
+    return v;
 }
 
 // One workgroup of kSmoothWG lanes per template (lanes over the K samples):
@@ -2453,88 +2507,89 @@ __device__ __forceinline__ void smooth_node(const MapP &m, int64_t t, int64_t r,
 // them in flight than one wave could.
 constexpr int kSmoothWG = 256;
 
-// The smooth statistic of one template at th[0..5] (readable by every lane)
-// and, with grad_out, its gradient; all kSmoothWG lanes of the workgroup call
-// it. Lane k sums samples k, k + kSmoothWG, ...; waves reduce by shuffles and
-// thread 0 adds the waves in order, so the result does not depend on timing.
-// Results (z, grad_out[0..5]) are valid in thread 0.
+// The smooth statistic of one template at th[0..5] (readable by every lane) and its gradient; all
+// kSmoothWG lanes of the workgroup call it. Lane k sums samples k, k + kSmoothWG, ...; waves reduce
+// by shuffles and the waves' sums are added in order, so the result does not depend on timing.
+// Results (z, grad[0..5]) are valid in the lanes of wave 0. rK = 1 / (K - 1) in FP64, 0 for K <= 1.
+// Bound by FP64 issue and, before it shared the phase of a row between its two nodes, took k / (K-1)
+// by one correction of k rK (exactly the quotient: rK is the rounded reciprocal, and quotients of
+// integers below 2^31 are not near a rounding boundary) and transposed the seven sums as they
+// shrink, by twice the sines and 84 LDS exchanges per wave.
 template <int MAPT>
-__device__ __forceinline__ void smooth_block(const MapP &m, const float *th, int K, double (*red)[7], float &z_out,
-                                             float *grad_out)
+__device__ __forceinline__ void smooth_block(const MapP &m, const float *th, int K, double rK, double (*red)[8],
+                                             float &z_out, float (&grad)[6])
 {
-    const int lane = threadIdx.x & 63;
     const double tau0 = th[0], tau2 = th[1], ph0 = th[2], ph1 = th[3], ph2 = th[4];
     const double dtau_s = (double)th[5] * 1e-3;
-    double z = 0, g0 = 0, g1 = 0, g2 = 0, g3 = 0, g4 = 0, g5 = 0;
+    double sum[8] = {};  // z, then the gradient
     for (int k = threadIdx.x; k < K; k += kSmoothWG) {
-        const double xi = K > 1 ? (double)k / (double)(K - 1) : 0.0;
+        const double kd = (double)k, q0 = kd * rK;
+        const double xi = fma(fma(-q0, (double)(K - 1), kd), rK, q0);
         const double b0 = (1 - xi) * (1 - xi), b1 = 2 * xi * (1 - xi), b2 = xi * xi;
         const double u0 = tau0 + xi * (tau2 - tau0), v0 = b0 * ph0 + b1 * ph1 + b2 * ph2 - 0.5;
         // clamp into the map (fmax/fmin also send a NaN coordinate to the lower edge)
         const double u = fmin(fmax(u0, 0.0), (double)(m.T - 1)), v = fmin(fmax(v0, 0.0), (double)(m.F - 1));
         const bool ut = u0 >= 0.0 && u0 <= (double)(m.T - 1), vt = v0 >= 0.0 && v0 <= (double)(m.F - 1);
-        int64_t i = (int64_t)floor(u), r = (int64_t)floor(v);
-        if (i > m.T - 2) i = m.T - 2;
-        if (r > m.F - 2) r = m.F - 2;
+        const int i = min((int)floor(u), m.T - 2), r = min((int)floor(v), m.F - 2);
         const double a = u - (double)i, b = v - (double)r;
+        const int64_t e = i * m.ld + r;
+        float2 p00, p01, p10, p11;
+        load_p2<MAPT>(m, e, p00, p01);
+        load_p2<MAPT>(m, e + m.ld, p10, p11);
+        const RowPhase h0 = row_phase(m, r, dtau_s), h1 = row_phase(m, r + 1, dtau_s);
         float G00, G10, G01, G11, D00, D10, D01, D11;
-        smooth_node<MAPT>(m, i, r, dtau_s, G00, D00);
-        smooth_node<MAPT>(m, i + 1, r, dtau_s, G10, D10);
-        smooth_node<MAPT>(m, i, r + 1, dtau_s, G01, D01);
-        smooth_node<MAPT>(m, i + 1, r + 1, dtau_s, G11, D11);
-        z += (1 - a) * (1 - b) * G00 + a * (1 - b) * G10 + (1 - a) * b * G01 + a * b * G11;
+        smooth_node(p00, h0, G00, D00);
+        smooth_node(p10, h0, G10, D10);
+        smooth_node(p01, h1, G01, D01);
+        smooth_node(p11, h1, G11, D11);
+        const double w00 = (1 - a) * (1 - b), w10 = a * (1 - b), w01 = (1 - a) * b, w11 = a * b;
+        sum[0] += w00 * G00 + w10 * G10 + w01 * G01 + w11 * G11;
         const double du = ut ? (1 - b) * (G10 - G00) + b * (G11 - G01) : 0.0;
         const double dv = vt ? (1 - a) * (G01 - G00) + a * (G11 - G10) : 0.0;
-        g0 += (1 - xi) * du;
-        g1 += xi * du;
-        g2 += b0 * dv;
-        g3 += b1 * dv;
-        g4 += b2 * dv;
-        g5 += ((1 - a) * (1 - b) * D00 + a * (1 - b) * D10 + (1 - a) * b * D01 + a * b * D11) * 1e-3;
+        sum[1] += (1 - xi) * du;
+        sum[2] += xi * du;
+        sum[3] += b0 * dv;
+        sum[4] += b1 * dv;
+        sum[5] += b2 * dv;
+        sum[6] += (w00 * D00 + w10 * D10 + w01 * D01 + w11 * D11) * 1e-3;
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        z += __shfl_xor(z, off);
-        g0 += __shfl_xor(g0, off);
-        g1 += __shfl_xor(g1, off);
-        g2 += __shfl_xor(g2, off);
-        g3 += __shfl_xor(g3, off);
-        g4 += __shfl_xor(g4, off);
-        g5 += __shfl_xor(g5, off);
-    }
-    if (lane == 0) {
-        double *r = red[threadIdx.x >> 6];
-        r[0] = z, r[1] = g0, r[2] = g1, r[3] = g2, r[4] = g3, r[5] = g4, r[6] = g5;
-    }
+    const double v = wave_sum8(sum);
+    if ((threadIdx.x & 63) < 8) red[threadIdx.x >> 6][threadIdx.x & 7] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int v = 1; v < kSmoothWG / 64; ++v) {
-            z += red[v][0], g0 += red[v][1], g1 += red[v][2], g2 += red[v][3];
-            g3 += red[v][4], g4 += red[v][5], g5 += red[v][6];
-        }
+    if (threadIdx.x < 64) {
         const double sc = K > 0 ? 1.0 / sqrt((double)K) : 0.0;
-        z_out = (float)(z * sc);
-        if (grad_out) {
-            grad_out[0] = (float)(g0 * sc);
-            grad_out[1] = (float)(g1 * sc);
-            grad_out[2] = (float)(g2 * sc);
-            grad_out[3] = (float)(g3 * sc);
-            grad_out[4] = (float)(g4 * sc);
-            grad_out[5] = (float)(g5 * sc);
+        float out[7];
+#pragma unroll
+        for (int q = 0; q < 7; ++q) {
+            double t = red[0][q];
+#pragma unroll
+            for (int w = 1; w < kSmoothWG / 64; ++w) t += red[w][q];
+            out[q] = (float)(t * sc);
         }
+        z_out = out[0];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) grad[q] = out[q + 1];
     }
 }
 
+__device__ __forceinline__ double sample_step(int K) { return K > 1 ? 1.0 / (double)(K - 1) : 0.0; }
+
 template <int MAPT>
-__global__ __launch_bounds__(kSmoothWG) void k_smooth_grad(MapP m, const float *theta, const int32_t *Ks, int32_t n,
+__global__ __launch_bounds__(kSmoothWG, 4) void k_smooth_grad(MapP m, const float *theta, const int32_t *Ks, int32_t n,
                                                            float *z_out, float *grad_out)
 {
-    __shared__ double red[kSmoothWG / 64][7];
+    __shared__ double red[kSmoothWG / 64][8];
     const int w = blockIdx.x;
     if (w >= n) return;  // whole workgroup
-    float z;
-    smooth_block<MAPT>(m, theta + (int64_t)w * 6, Ks[w], red, z, grad_out ? grad_out + (int64_t)w * 6 : nullptr);
-    if (threadIdx.x == 0) z_out[w] = z;
+    const int K = Ks[w];
+    float z, g[6];
+    smooth_block<MAPT>(m, theta + (int64_t)w * 6, K, sample_step(K), red, z, g);
+    if (threadIdx.x == 0) {
+        z_out[w] = z;
+        if (grad_out) {
+            for (int q = 0; q < 6; ++q) grad_out[(int64_t)w * 6 + q] = g[q];
+        }
+    }
 }
 
 // ---------------------------------------------------------------- refinement helpers
@@ -2615,31 +2670,38 @@ __device__ __forceinline__ void refine_move(float *th, const float *g, int32_t s
 // best), and, while s < steps, take ascent step s. theta holds the start on
 // entry and the best point on exit; best_z receives its smooth statistic.
 template <int MAPT>
-__global__ __launch_bounds__(kSmoothWG) void k_refine(MapP m, float *theta, const int32_t *Ks, int32_t n,
+__global__ __launch_bounds__(kSmoothWG, 4) void k_refine(MapP m, float *theta, const int32_t *Ks, int32_t n,
                                                       float *best_z, RefineP p)
 {
-    __shared__ double red[kSmoothWG / 64][7];
+    __shared__ double red[kSmoothWG / 64][8];
     __shared__ float cur[6];
     const int w = blockIdx.x;
     if (w >= n) return;  // whole workgroup
     float *th_io = theta + (int64_t)w * 6;
-    if (threadIdx.x == 0) {
+    float th[6], best[6], bz = 0.0f, z, g[6];  // of wave 0, the same in all its lanes
+    if (threadIdx.x < 64) {
         double t[6];
         for (int q = 0; q < 6; ++q) t[q] = th_io[q];
         project_theta(t, p);
-        for (int q = 0; q < 6; ++q) cur[q] = (float)t[q];
+        for (int q = 0; q < 6; ++q) th[q] = best[q] = (float)t[q];
+        if (threadIdx.x == 0)
+            for (int q = 0; q < 6; ++q) cur[q] = th[q];
     }
     __syncthreads();
     const int K = Ks[w];
-    float best[6], bz = 0.0f, z, g[6];
+    const double rK = sample_step(K);
     for (int32_t s = 0; s <= p.steps; ++s) {
-        smooth_block<MAPT>(m, cur, K, red, z, g);
-        if (threadIdx.x == 0) {
+        smooth_block<MAPT>(m, cur, K, rK, red, z, g);
+        if (threadIdx.x < 64) {
             if (s == 0 || z > bz) {
                 bz = z;
-                for (int q = 0; q < 6; ++q) best[q] = cur[q];
+                for (int q = 0; q < 6; ++q) best[q] = th[q];
             }
-            if (s < p.steps) refine_move(cur, g, s, p);
+            if (s < p.steps) {
+                refine_move(th, g, s, p);
+                if (threadIdx.x == 0)
+                    for (int q = 0; q < 6; ++q) cur[q] = th[q];
+            }
         }
         __syncthreads();  // the new point is visible; red may be reused
     }

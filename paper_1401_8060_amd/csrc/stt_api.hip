@@ -910,7 +910,7 @@ stt_status topk_launch(stt_ctx *c, SRC src, int64_t n, int64_t first, int32_t K,
         hipLaunchKernelGGL(k_topk_hist<SRC>, dim3(grid), dim3(256), 0, c->stream, src, n, (uint64_t)first, st, pass);
     hipLaunchKernelGGL(k_topk_gather<SRC>, dim3(grid), dim3(256), 0, c->stream, src, n, (uint64_t)first, st, cand);
     const unsigned rgrid = (unsigned)((std::min<int64_t>(n, kTopkCand) + 63) / 64);
-    hipLaunchKernelGGL(k_topk_rank, dim3(rgrid), dim3(256), 0, c->stream, (const TopkState *)st, (const uint64_t *)cand, K,
+    hipLaunchKernelGGL(k_topk_rank, dim3(rgrid), dim3(1024), 0, c->stream, (const TopkState *)st, (const uint64_t *)cand, K,
                        last_only, idx_dev, val_dev);
     STT_HIP(c, hipGetLastError());
     return STT_OK;
@@ -1297,7 +1297,7 @@ stt_status stt_map_pack_p16(stt_ctx *c, const stt_map *map, void *out_dev, int64
     const int64_t n = (int64_t)map->T * map->F;
     const unsigned grid = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, c->stream, (uint32_t *)amax, (int64_t)2, 0u);
-    hipLaunchKernelGGL(k_absmax_p, dim3(grid), dim3(256), 0, c->stream, m, amax);
+    hipLaunchKernelGGL(k_absmax_p, dim3(std::min(grid, 1024u)), dim3(256), 0, c->stream, m, amax);
     STT_HIP(c, hipGetLastError());
     unsigned long long bits = 0;
     STT_HIP(c, hipMemcpyAsync(&bits, amax, sizeof bits, hipMemcpyDeviceToHost, c->stream));

@@ -378,7 +378,7 @@ stt_status stt_score_batch(stt_ctx *ctx, const stt_map *maps_host, int32_t n_map
 stt_status stt_set_graph(stt_ctx *ctx, int32_t on);
 
 /* Autotuner of the slab scorer: times every compiled workgroup shape with LDS
- * slab budgets of 160, 112, 80 and 48 KB on `n` templates from `gen` on this
+ * slab budgets of 160, 112, 80, 48 and 40 KB on `n` templates from `gen` on this
  * map (one warm-up and three timed calls each, HIP events, kernel time only),
  * applies the fastest to the context (stt_set_slab_shape, stt_set_path's
  * lds_bytes) and writes it as choice_out[3] = {wg, tpt, lds_bytes} (host,

@@ -2030,9 +2030,9 @@ int log2_floor(int64_t v)
 }
 
 // Generation of the scorers' inner loop: part of every cache key, so that choices timed on an
-// earlier loop are searched again. "pol2": polar folded map, one cosine per pixel, slab scorers
-// held to 128 VGPRs (4 waves per SIMD).
-constexpr const char *kCoreTag = "pol2";
+// earlier loop are searched again. "pol3": polar folded map, one cosine per pixel, rows carried by one
+// FP64 add (lazy rows), slabs streamed by scalar-addressed DMA, two templates per lane at 64 VGPRs.
+constexpr const char *kCoreTag = "pol3";
 
 // maps of similar duration (power-of-two bucket) and call size share a choice
 std::string tune_key(const stt_ctx *c, const stt_map *m, int64_t n)
@@ -2068,7 +2068,7 @@ stt_status tune_search(stt_ctx *c, int F, int reps, const std::function<stt_stat
     c->use_graph = false;
     c->recs.clear();
     c->next = saved_next;  // tuning events come after any the caller has not read yet
-    static const int ldss[] = {160 * 1024, 112 * 1024, 80 * 1024, 48 * 1024};
+    static const int ldss[] = {160 * 1024, 112 * 1024, 80 * 1024, 48 * 1024, 40 * 1024};
     stt_status s = STT_OK;
     for (const auto &sh : kShapes) {
         for (int lds : ldss) {

@@ -609,15 +609,20 @@ stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, 
     return STT_OK;
 }
 
-// Wave-per-template calls whose templates together hold fewer pixels than the map gather from the
-// caller's FP32 map and form the polar elements as they go; others fold the map first (9 us for 1000
-// x 1000). A template holds up to T pixels, so n <= F keeps the gathers below the map's T x F
-// pixels. One lane per template always folds: its polar forms would follow one another (326 us
-// folded, 629 us not, for 1000 templates on 1000 x 1000). FP16 maps are gathered as they are by
-// every direct scorer: their words are the polar elements.
+// Wave-per-template calls that score fewer pixels than a large map holds gather from the caller's
+// FP32 map and form the polar elements as they go; others fold the map first (10 us for 1000 x 1000;
+// 4 us, a launch, for small ones). Measured, folded and not (us): below some 250 000 pixels folding
+// is better at any n (9.1 and 18.5 for 128 templates on 100 x 128, 9.5 and 11.5 for 450 on
+// 300 x 300); above, gathering is up to n T = 1.2e6 (20.7 and 16.2 for 1000 on 1000 x 1000, 13.2 and
+// 11.2 for 600 on 300 x 1000; with templates of all T columns 24.9 and 20.8 at 1000, 26.6 and 28.8 at
+// 1500). Past 64 flush groups a lane's second group waits for its first's polar forms: folding is
+// better (500 templates on 2000 x 500: 24.1 and 27.5). One lane per template always folds: its polar
+// forms would follow one another (326 us folded, 629 us not, for 1000 templates on 1000 x 1000). FP16
+// maps are gathered as they are by every direct scorer: their words are the polar elements.
 bool gather_unfolded(const stt_map *map, bool per_wave, int64_t n)
 {
-    return map->dtype == STT_P16 || (per_wave && n <= map->F);
+    if (map->dtype == STT_P16) return true;
+    return per_wave && map->T <= 64 * kFlush && (int64_t)map->T * map->F >= 250000 && n * map->T <= 1200000;
 }
 
 // Which scorer takes a call of n templates on T columns. The slab scorer sweeps the columns one slab

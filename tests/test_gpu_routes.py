@@ -138,3 +138,23 @@ def test_slab_shapes_by_size(stt, F):
         b.close()
     assert np.array_equal(keys[0], keys[1])
     c.close()
+
+
+# both sides of the rule by which a wave per template gathers from the caller's map or folds it first:
+# 250 000 pixels, 1024 columns, n T = 1.2e6
+@pytest.mark.parametrize("T,F,n", [(500, 499, 2000), (500, 500, 2000), (500, 500, 2400), (500, 500, 2401),
+                                   (1024, 245, 1171), (1024, 245, 1172), (1025, 245, 1000)])
+def test_wave_scorers_folded_or_not(stt, ctx, T, F, n):
+    m = _map(stt, T, F)
+    tr = _tracks(ctx, stt, T, F, n)
+    print("folded or not", T, F, n, flush=True, file=sys.stderr)
+    got = []
+    for path in (3, 1):
+        ctx.set_path(path)
+        z, key = ctx.score(m, tracks=tr)
+        zd, mi, keyd = ctx.score_maxdelay(m, -DT, DT // 8, 9, tracks=tr)
+        got.append((_host(z, zd, mi), key_to_host(key), key_to_host(keyd)))
+    ctx.set_path(0)
+    for a, b in zip(got[0][0], got[1][0]):
+        assert np.array_equal(a, b)
+    assert got[0][1:] == got[1][1:]

@@ -211,7 +211,7 @@ stt_status stt_score_noalloc(stt_ctx *ctx, const stt_map *map, const stt_gen *ge
  * t the row is floor(f(xi)/256), xi the root in [0, 1] of t(xi) = t, computed
  * exactly (an FP32 evaluation inside a certified error window, else FP64
  * Newton refinement of the root, else an exact 128-bit integer decision).
- * Generated templates (from 4096 on, when two slabs of a column fit 80 KB) are
+ * Generated templates (larger calls, when two slabs of a column fit 80 KB) are
  * binned by time extent and scored from LDS slabs; given lists and small
  * calls take one wave per template. Both give the same bits. */
 stt_status stt_make_tracks_tm(stt_ctx *ctx, const stt_gen *gen, int32_t T, int32_t F, int64_t first, int64_t n,

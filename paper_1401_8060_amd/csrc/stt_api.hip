@@ -635,6 +635,19 @@ bool gather_unfolded(const stt_map *map, bool per_wave, int64_t n)
 bool prefer_slabs(int T, int64_t n) { return n >= 4096 && n * (int64_t)T >= 60000000; }
 bool prefer_wave(int T, int64_t n) { return n * (int64_t)(T + 600) < 80000 * (int64_t)T; }
 
+// The same for the delay grid, per launch of 8 delays. A slab call costs at least 72, 162, 220, 432,
+// 728 us at T = 100, 300, 500, 1000, 2000 (F = 128, 1000, 500, 1000, 500); the cheaper direct scorer
+// reaches that at 4 x 10^5, 2 x 10^5, 1.65 x 10^5, 1.55 x 10^5, 1.7 x 10^5 templates (at 10^5: 37, 99,
+// 161, 288, 454 us). One wave per template costs 2.35 ns each, one lane per template 0.16 T us and
+// 0.00185 T ns each: they cross at 7 x 10^3, 2.7 x 10^4, 5.6 x 10^4 for T = 100, 300, 500, and for
+// T > 1270 one wave per template is always better (10^5 at T = 1000: 288 and 360 us).
+bool prefer_slabs_md(int T, int64_t n) { return n >= 130000 + 27000000 / T; }
+bool prefer_wave_md(int T, int64_t n) { return n * (47000 - 37 * (int64_t)T) < 3200000 * (int64_t)T; }
+
+// And for free-t_mid templates, whose slab call costs at least 62, 138, 160, 345, 495 us at those T;
+// one wave per template costs 1.7 to 4.5 ns each, 37 to 74 us at 10^4 and 191, 200, 209, 306, 493 at 10^5.
+bool prefer_slabs_tm(int T, int64_t n) { return n >= 4096 && n * (int64_t)(T + 600) >= 165000 * (int64_t)T; }
+
 template <bool EXPL>
 stt_status score_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Trk *tr, int64_t first, int64_t n,
                       int32_t norm, float *snr, uint64_t *best, const FixedBufs *fb = nullptr)
@@ -775,7 +788,7 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     const int esize = fold_esize(map->dtype);
     const int64_t ldc = fold_ld(map->F, esize);
     bool slab = c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
-                (c->path == 2 || n >= 4096);
+                (c->path == 2 || prefer_slabs_md(map->T, n));
     if (c->path == 2 && !slab)
         return fail(c, STT_EUNSUPPORTED, "F=%d too wide for two LDS slabs of %d bytes", map->F, lds);
     stt_status s;
@@ -787,7 +800,7 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
     const bool p16 = map->dtype == STT_P16;
-    const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave(map->T, n));
+    const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave_md(map->T, n));
     if (!slab && gather_unfolded(map, per_wave, n * ((n_tau + kMD - 1) / kMD))) {
         const MapP m = to_mapp(map);
         s = p16 ? maxdelay_direct<EXPL, kMapP16>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best)
@@ -1249,7 +1262,7 @@ stt_status stt_score_tm(stt_ctx *c, const stt_map *map, const stt_gen *gen, cons
     const int esize = fold_esize(map->dtype);
     const int64_t ldc = fold_ld(map->F, esize);
     const bool slab = !tracks_dev && c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
-                      (c->path == 2 || n >= 4096);
+                      (c->path == 2 || prefer_slabs_tm(map->T, n));
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
     const bool p16 = map->dtype == STT_P16;

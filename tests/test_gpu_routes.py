@@ -158,3 +158,38 @@ def test_wave_scorers_folded_or_not(stt, ctx, T, F, n):
     for a, b in zip(got[0][0], got[1][0]):
         assert np.array_equal(a, b)
     assert got[0][1:] == got[1][1:]
+
+
+# both sides of the template counts at which the delay grid (T = 100: one wave to one lane per
+# template near 7391, slabs from 400 000) and the free-t_mid scorer (slabs from 23 572) change scorers
+@pytest.mark.parametrize("n", [7390, 7392, 399_999, 400_000])
+def test_delay_grid_routes_by_size(stt, ctx, n):
+    m = _map(stt, 100, 64)
+    g = stt.Gen(seed=13, min_len=10, dtau_max=DT)
+    got = []
+    for path in (0, 1, 2):
+        print("delay route", n, path, flush=True, file=sys.stderr)
+        ctx.set_path(path)
+        z, mi, key = ctx.score_maxdelay(m, -DT, DT // 4, 9, gen=g, n=n, first=3)
+        got.append((*_host(z, mi), key_to_host(key)))
+    ctx.set_path(0)
+    for z, mi, key in got[1:]:
+        assert np.array_equal(z, got[0][0]) and np.array_equal(mi, got[0][1]) and key == got[0][2]
+
+
+@pytest.mark.parametrize("p16", [False, True], ids=["f32", "p16"])
+@pytest.mark.parametrize("n", [4095, 23_571, 23_572, 60_000])
+def test_tmid_routes_by_size(stt, ctx, n, p16):
+    m = _map(stt, 100, 64)
+    if p16:
+        m = ctx.pack_p16(m)
+    g = stt.Gen(seed=14, min_len=10, dtau_max=DT)
+    got = []
+    for path in (0, 2, 3):
+        print("t_mid route", n, p16, path, flush=True, file=sys.stderr)
+        ctx.set_path(path)
+        z, key = ctx.score_tm(m, gen=g, n=n, first=3)
+        got.append((*_host(z), key_to_host(key)))
+    ctx.set_path(0)
+    for z, key in got[1:]:
+        assert np.array_equal(z, got[0][0]) and key == got[0][1]

@@ -48,11 +48,12 @@ LDS_RANDOM_GBS = 51000.0
 FAR_READ_GBS = 6800.0
 # Instructions of the inner loop per template pixel (one template, one column), by issue class:
 #   plain scorer, FP32 map (polar fold): the row of Eq. 6 by the exact FP64 recurrence (1 FMA,
-#   2 adds), its LDS address (shift-add), the phase of Eq. 8 plus arg p (integer multiply, add3),
-#   the phase as FP32 turns (funnel shift): 7 full-rate; the cosine: 1 transcendental; the term's
-#   FMA: 1 double-rate. FP16 map: the term takes its binary16 magnitude in a mixed FMA (full rate).
-CORE_MIX = {"full": 7, "double": 1, "trans": 1}
-CORE_MIX_P16 = {"full": 8, "double": 0, "trans": 1}
+#   1 add; it is seeded anew every few columns), its LDS address (shift-add), the phase of Eq. 8 plus
+#   arg p (integer multiply, add3), the phase as FP32 turns (funnel shift): 6 full-rate; the cosine:
+#   1 transcendental; the term's FMA: 1 double-rate. FP16 map: the term takes its binary16 magnitude
+#   in a mixed FMA (full rate).
+CORE_MIX = {"full": 6, "double": 1, "trans": 1}
+CORE_MIX_P16 = {"full": 7, "double": 0, "trans": 1}
 #   free t_mid: the row is an independent root per column -- D = b^2 + 4 a dt and 2 dt carried by
 #   one add each (2 double), D as FP32 (full), square root and reciprocal of the reduced root
 #   2 dt / (b + sqrt(D)) (2 transcendental; its add, multiply and the two FMAs of the Bezier value:
@@ -306,7 +307,11 @@ def run_single(args, name, w):
                           "injection": w["inject"] is not None, "per_track_snr": snr is not None, "map_sha256": sha[:16],
                           "slab_shape": list(choice) if choice else None})
     out["best"] = {"z": zk, "j": jk}
-    out["roofline"] = roofline("k_score_slab" if n >= 4096 else "k_score_direct", kern_ms, px, BYTES_F32,
+    # the scorer that the library's rule by pixels and templates gives this call
+    T = w["T"]
+    kernel = ("k_score_slab" if n >= 4096 and n * T >= 60_000_000 else
+              "k_score_wave" if n * (T + 600) < 80_000 * T else "k_score_direct")
+    out["roofline"] = roofline(kernel, kern_ms, px, BYTES_F32,
                                measured_traffic(name + ("_argmax" if snr is None else ""), choice))
     if snr is not None and not args.no_argmax_leg:
         # the search proper keeps only the loudest template (Sec. III, V): the same steps with no
@@ -593,7 +598,7 @@ def run_mapform(args, name, w):
     timed(argparse.Namespace(warmup=0, steps=args.steps), step_fn, torch)
     call_ms, ncall = ctx.kernel_ms_total(stt.STAGE_CALL)
     ctx.set_timing(False)
-    launches = (ns + 15) // 16
+    launches = (ns + 63) // 64  # up to 64 slides each
     spectra_ms = call_ms / args.steps - form_ms  # the two stt_spectra calls of a step
     launch_ms = form_ms / launches
     px = ns * T * F
@@ -601,7 +606,7 @@ def run_mapform(args, name, w):
         f"({launches} launches of k_form_maps, {launch_ms * 1e3:.1f} us each)")
     # algorithmic bytes of one k_form_maps launch: its slides' maps written (8 B Y + 4 B sigma per
     # pixel) and both detectors' spectra and P' read once (2 x 12 B per pixel)
-    per_launch = [min(16, ns - k) for k in range(0, ns, 16)]
+    per_launch = [min(64, ns - k) for k in range(0, ns, 64)]
     bytes_launch = sum(12 * T * F * m + 24 * T * F for m in per_launch) / launches
     achieved = bytes_launch / (launch_ms * 1e-3) / 1e9
     fq4_lo, dfq4 = p.fq4()

@@ -1474,6 +1474,8 @@ stt_status stt_spectra(stt_ctx *c, const stt_spectro *p, const float *strain_dev
     int lg = 0;
     while ((1 << lg) < N) ++lg;
     ev_record(c, 4);
+    // a lane holds 8 points at a time. 1000 columns of 4096 samples: 28 us a stage at a time through LDS,
+    // 15 us with three stages in registers; the power sums 11 and 7.5 us (a column, four columns a lane).
     const int fft_wg = std::min(kFftThreads, std::max(64, N / 8));
     hipLaunchKernelGGL(k_col_fft, dim3(T), dim3(fft_wg), sizeof(float2) * fft_slot(N), c->stream, strain_dev, p->M, lg,
                        p->k_lo, p->F, (float)(1.0 / p->fs), (const float2 *)c->fft_tab, (float2 *)spec_dev);
@@ -1997,6 +1999,9 @@ stt_status stt_refine(stt_ctx *c, const stt_map *map, int32_t min_len, int32_t d
     mf.sig = nullptr;
     mf.ld = ldc;
     ev_record(c, 0);
+    // 1024 templates x 51 evaluations on 1000 x 1000: 335 us with a phase per node, an FP64 division per
+    // sample and 84 exchanges per wave; 283 us without; 245 us with its registers held to 128, so that 4
+    // instead of 3 workgroups share a CU and 1024 templates run in one round.
     hipLaunchKernelGGL(k_refine<kMapPF>, dim3((unsigned)n), dim3(kSmoothWG), 0, c->stream, mf, theta_dev, K_dev, n,
                        z_smooth_dev, p);
     STT_HIP(c, hipGetLastError());

@@ -147,7 +147,7 @@ stt_status stt_set_path(stt_ctx *ctx, int32_t path, int32_t lds_bytes);
 
 /* Shape of the LDS-slab scorer: wg lanes per workgroup and tpt templates per
  * lane; STT_EUNSUPPORTED for a shape not compiled in (1024x4, 512x4, 256x4,
- * 1024x2, 512x2). Default 1024x4. */
+ * 1024x2, 512x2). Default: by the size of each call. */
 stt_status stt_set_slab_shape(stt_ctx *ctx, int32_t wg, int32_t tpt);
 
 /* Slab staging. Every scoring call first folds the map into a context-owned

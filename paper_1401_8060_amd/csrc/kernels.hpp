@@ -901,6 +901,9 @@ template <> __device__ __forceinline__ uint32_t lds_elem<uint32_t>(uint32_t addr
 // waits for them. Addresses stay scalar (base in SGPRs, the lane's 16 bytes as the vector offset):
 // with the 64-bit vector address and the generic LDS pointer of a plain builtin the loop around a
 // copy took 52 scalar instructions per wave and slab, and the search scorer 6-8 % more time.
+// The compiler keeps no wait states inside an asm block: gfx9 wants one between a scalar write of M0 and
+// the copy that reads it, and five between a vector instruction's write of a scalar register and a vector
+// memory address in it. The move of the address in between is the one, and makes a scalar write of the other.
 template <int NW>
 struct SlabDma {
     const char *src;    // this wave's first piece of column 0
@@ -925,9 +928,11 @@ struct SlabDma {
         const uint32_t bytes = (uint32_t)__builtin_amdgcn_readfirstlane(ncol) * col_bytes;
         const char *p = src + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(c0) * col_bytes;
         const uint32_t d = __builtin_amdgcn_readfirstlane(dst);
-        for (uint32_t o = wave_off; o < bytes; o += NW * kDmaBytes, p += NW * kDmaBytes)
-            asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-                         : : "v"(lane_off), "s"(p), "s"(d + o) : "memory", "m0");
+        for (uint32_t o = wave_off; o < bytes; o += NW * kDmaBytes, p += NW * kDmaBytes) {
+            const char *q;
+            asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                         : "=&s"(q) : "v"(lane_off), "s"(p), "s"(d + o) : "memory", "m0");
+        }
     }
 };
 

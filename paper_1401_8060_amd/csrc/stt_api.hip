@@ -934,21 +934,25 @@ stt_status topk_launch(stt_ctx *c, SRC src, int64_t n, int64_t first, int32_t K,
     return STT_OK;
 }
 
+// Whether the context's stream captures a graph, or cannot say (the null stream while another captures).
+bool capturing(stt_ctx *c)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // Counts (and FAP = count / n_ref) of n_q query keys against n_ref reference keys: directly up to
 // kLouderDirect references, else by ranks in passes of kRankTiles tiles of queries. The ranks need
-// scratch; a call that cannot have it (no memory, or not yet allocated on a capturing stream) counts
-// directly too.
+// scratch. A call that cannot have it counts directly too, and so does one on a capturing stream: its
+// graph would keep the scratch's address, and the scratch moves when a later call needs more of it.
 stt_status count_louder(stt_ctx *c, const uint64_t *ref, int64_t n_ref, const uint64_t *q, int64_t n_q, int64_t *count,
                         float *fap)
 {
     const int64_t per_pass = (int64_t)kRankTile * kRankTiles;
     const size_t need = sizeof(RankTile) * (size_t)std::min<int64_t>(kRankTiles, (n_q + kRankTile - 1) / kRankTile);
-    bool ranks = n_ref > kLouderDirect;
-    if (ranks && need > c->mdbuf_bytes) {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) (void)hipGetLastError();
-        ranks = cs == hipStreamCaptureStatusNone && ensure_mdbuf(c, need) == STT_OK;
-    }
+    const bool ranks = n_ref > kLouderDirect && !capturing(c) && ensure_mdbuf(c, need) == STT_OK;
     if (!ranks) {
         hipLaunchKernelGGL(k_count_louder, dim3((unsigned)((n_q + 255) / 256)), dim3(256), 0, c->stream, ref, n_ref, q, n_q,
                            count, fap, (double)n_ref);

@@ -1,0 +1,94 @@
+// Host harness around the library's host side (stt_api.hip) with the HIP runtime replaced by a
+// recorder: no GPU is touched. Reads commands from stdin, prints one line for each.
+//   louder n_ref n_q have cap malloc sync -> the counts' status, allocations and launched kernels, with
+//       `have` bytes of scratch, a stream that captures (cap 1) or whose query fails (cap 2), and these
+//       statuses of hipMalloc and hipStreamSynchronize
+#include <hip/hip_ext.h>
+#include <hip/hip_runtime.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <string>
+#include <vector>
+
+namespace fake {
+std::string launches;
+int n_malloc = 0;
+hipError_t malloc_status = hipSuccess, sync_status = hipSuccess, capture_query = hipSuccess;
+hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+
+hipError_t Malloc(void **p, size_t bytes)
+{
+    ++n_malloc;
+    if (malloc_status != hipSuccess) return malloc_status;
+    *p = std::malloc(bytes);
+    return hipSuccess;
+}
+hipError_t Free(void *p)
+{
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t IsCapturing(hipStream_t, hipStreamCaptureStatus *s)
+{
+    *s = capture;
+    return capture_query;
+}
+void launch(const char *kernel, dim3 grid)
+{
+    launches += " " + std::string(kernel) + ":" + std::to_string(grid.x);
+}
+void reset()
+{
+    launches.clear();
+    n_malloc = 0;
+    malloc_status = sync_status = capture_query = hipSuccess;
+    capture = hipStreamCaptureStatusNone;
+}
+}  // namespace fake
+
+#define hipMalloc(p, n) fake::Malloc((void **)(p), n)
+#define hipFree(p) fake::Free(p)
+#define hipSetDevice(d) hipSuccess
+#define hipGetLastError() hipSuccess
+#define hipStreamSynchronize(s) fake::sync_status
+#define hipStreamIsCapturing(s, p) fake::IsCapturing(s, p)
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(kern, grid, ...) fake::launch(#kern, grid)
+
+#include "stt_api.hip"
+
+static int louder()
+{
+    long long n_ref, n_q, have;
+    int cap, m, s;
+    if (std::scanf("%lld %lld %lld %d %d %d", &n_ref, &n_q, &have, &cap, &m, &s) != 6) return 2;
+    fake::reset();
+    stt_ctx c;
+    if (have && ensure_mdbuf(&c, (size_t)have) != STT_OK) return 2;
+    fake::n_malloc = 0;
+    fake::capture = cap == 1 ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    fake::capture_query = cap == 2 ? hipErrorStreamCaptureImplicit : hipSuccess;
+    fake::malloc_status = (hipError_t)m;
+    fake::sync_status = (hipError_t)s;
+    const stt_status st = count_louder(&c, nullptr, n_ref, nullptr, n_q, nullptr, nullptr);
+    std::printf("%d %d%s\n", st, fake::n_malloc, fake::launches.c_str());
+    return 0;
+}
+
+int main()
+{
+    char cmd[16];
+    while (std::scanf("%15s", cmd) == 1)
+        if (std::strcmp(cmd, "louder") || louder()) return 2;
+    return 0;
+}
+
+// The device code's registration, which would reach for a GPU.
+extern "C" {
+void **__hipRegisterFatBinary(const void *) { static void *h = nullptr; return &h; }
+void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void **) {}
+}

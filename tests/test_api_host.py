@@ -1,0 +1,45 @@
+"""The library's host side (stt_api.hip) with the HIP runtime replaced by a recorder: what it allocates and
+launches, without a GPU."""
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+RANKS = ["k_rank_sort:1", "k_rank_count:1", "k_rank_finish:1"]
+DIRECT = ["k_count_louder:1"]
+
+
+@pytest.fixture(scope="module")
+def api(tmp_path_factory):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    out = tmp_path_factory.mktemp("api") / "api"
+    subprocess.run([hipcc, "--cuda-host-only", "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-w",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1401_8060_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "helpers", "api_host.cpp"), "-o", str(out)],
+                   check=True, capture_output=True)
+
+    def run(line):
+        r = subprocess.run([str(out)], input=line + "\n", capture_output=True, text=True, check=True)
+        return r.stdout.split()
+    return run
+
+
+def test_counts_take_ranks_above_the_direct_limit(api):
+    assert api("louder 512 10 0 0 0 0") == ["0", "0", *DIRECT]
+    assert api("louder 513 10 0 0 0 0") == ["0", "1", *RANKS]
+    assert api("louder 513 10 9999999 0 0 0") == ["0", "0", *RANKS]
+
+
+@pytest.mark.parametrize("cap", [1, 2])
+@pytest.mark.parametrize("have", [0, 9_999_999])
+def test_captured_counts_use_no_scratch(api, cap, have):
+    """A graph keeps the addresses it was captured with, and the scratch moves when a later call needs more of
+    it: captured counts have to do without, also where it is large enough already (cap 2: the stream cannot be
+    asked, as the null stream while another one captures)."""
+    assert api(f"louder 1000 10 {have} {cap} 0 0") == ["0", "0", *DIRECT]

@@ -945,14 +945,23 @@ bool capturing(stt_ctx *c)
 
 // Counts (and FAP = count / n_ref) of n_q query keys against n_ref reference keys: directly up to
 // kLouderDirect references, else by ranks in passes of kRankTiles tiles of queries. The ranks need
-// scratch. A call that cannot have it counts directly too, and so does one on a capturing stream: its
+// scratch. A call that finds no memory for it counts directly too, and so does one on a capturing stream: its
 // graph would keep the scratch's address, and the scratch moves when a later call needs more of it.
 stt_status count_louder(stt_ctx *c, const uint64_t *ref, int64_t n_ref, const uint64_t *q, int64_t n_q, int64_t *count,
                         float *fap)
 {
     const int64_t per_pass = (int64_t)kRankTile * kRankTiles;
     const size_t need = sizeof(RankTile) * (size_t)std::min<int64_t>(kRankTiles, (n_q + kRankTile - 1) / kRankTile);
-    const bool ranks = n_ref > kLouderDirect && !capturing(c) && ensure_mdbuf(c, need) == STT_OK;
+    bool ranks = n_ref > kLouderDirect && !capturing(c);
+    if (ranks) {
+        const std::string before = c->err;
+        const stt_status s = ensure_mdbuf(c, need);
+        if (s != STT_OK && s != STT_ENOMEM) return s;
+        if (s == STT_ENOMEM) {
+            ranks = false;
+            c->err = before;
+        }
+    }
     if (!ranks) {
         hipLaunchKernelGGL(k_count_louder, dim3((unsigned)((n_q + 255) / 256)), dim3(256), 0, c->stream, ref, n_ref, q, n_q,
                            count, fap, (double)n_ref);

@@ -1,6 +1,7 @@
 // Host harness around the library's host side (stt_api.hip) with the HIP runtime replaced by a
 // recorder: no GPU is touched. Reads commands from stdin, prints one line for each.
-//   louder n_ref n_q have cap malloc sync -> the counts' status, allocations and launched kernels, with
+//   louder n_ref n_q have cap malloc sync -> the counts' status, allocations, launched kernels and "message" if an
+//       error message is left, with
 //       `have` bytes of scratch, a stream that captures (cap 1) or whose query fails (cap 2), and these
 //       statuses of hipMalloc and hipStreamSynchronize
 #include <hip/hip_ext.h>
@@ -73,7 +74,7 @@ static int louder()
     fake::malloc_status = (hipError_t)m;
     fake::sync_status = (hipError_t)s;
     const stt_status st = count_louder(&c, nullptr, n_ref, nullptr, n_q, nullptr, nullptr);
-    std::printf("%d %d%s\n", st, fake::n_malloc, fake::launches.c_str());
+    std::printf("%d %d%s%s\n", st, fake::n_malloc, fake::launches.c_str(), c.err.empty() ? "" : " message");
     return 0;
 }
 

@@ -43,3 +43,17 @@ def test_captured_counts_use_no_scratch(api, cap, have):
     it: captured counts have to do without, also where it is large enough already (cap 2: the stream cannot be
     asked, as the null stream while another one captures)."""
     assert api(f"louder 1000 10 {have} {cap} 0 0") == ["0", "0", *DIRECT]
+
+
+HIP_OOM, HIP_FAULT = 2, 719  # hipErrorOutOfMemory, hipErrorLaunchFailure
+EHIP = "-4"  # STT_EHIP
+
+
+def test_counts_without_memory_are_direct(api):
+    """Out of memory leaves the direct counts, and no message of a failure that the caller never sees."""
+    assert api(f"louder 1000 10 0 0 {HIP_OOM} 0") == ["0", "1", *DIRECT]
+
+
+def test_counts_report_a_failed_stream(api):
+    """The scratch waits for the stream before it moves; what the wait reports is the call's status."""
+    assert api(f"louder 1000 10 64 0 0 {HIP_FAULT}") == [EHIP, "0", "message"]

@@ -1535,14 +1535,20 @@ stt_status stt_form_maps(stt_ctx *c, const stt_spectro *p, int32_t T, const floa
     // a launch holds below 2^32 lanes: at least 15 slides of the largest map
     const int64_t slide_wgs = 8 * ((nchunk + 7) / 8);
     const int per_launch = (int)std::min<int64_t>(kSlidesPerLaunch, (((int64_t)1 << 24) - 1) / slide_wgs);
-    for (int k0 = 0; k0 < n_slides; k0 += per_launch) {
+    // a launch writes its slides in no order: a buffer that comes again starts the next launch, so that
+    // the last slide into it stands
+    const auto taken = [](const SlideArgs &a, const float *Y, const float *sigma) {
+        for (int k = 0; k < a.n; ++k)
+            if ((const float *)a.Y[k] == Y || a.sigma[k] == sigma) return true;
+        return false;
+    };
+    for (int k0 = 0; k0 < n_slides;) {
         SlideArgs a{};
-        a.n = std::min(per_launch, n_slides - k0);
-        for (int k = 0; k < a.n; ++k) {
-            a.Y[k] = (float2 *)Y_dev[k0 + k];
-            a.sigma[k] = sigma_dev[k0 + k];
-            const int64_t sh = shifts[k0 + k] % T;
-            a.shift[k] = (int32_t)(sh < 0 ? sh + T : sh);
+        for (; k0 < n_slides && a.n < per_launch && !taken(a, Y_dev[k0], sigma_dev[k0]); ++k0, ++a.n) {
+            a.Y[a.n] = (float2 *)Y_dev[k0];
+            a.sigma[a.n] = sigma_dev[k0];
+            const int64_t sh = shifts[k0] % T;
+            a.shift[a.n] = (int32_t)(sh < 0 ? sh + T : sh);
         }
         const dim3 grid((unsigned)(slide_wgs * a.n));
         if (pair)

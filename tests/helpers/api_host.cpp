@@ -4,6 +4,8 @@
 //       error message is left, with
 //       `have` bytes of scratch, a stream that captures (cap 1) or whose query fails (cap 2), and these
 //       statuses of hipMalloc and hipStreamSynchronize
+//   slides T F n (y s) x n -> status of stt_form_maps of n slides into buffers number y (Y) and s (sigma),
+//       F even, and the slides of each launch
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -15,6 +17,7 @@
 
 namespace fake {
 std::string launches;
+std::vector<unsigned> grids;
 int n_malloc = 0;
 hipError_t malloc_status = hipSuccess, sync_status = hipSuccess, capture_query = hipSuccess;
 hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -39,10 +42,12 @@ hipError_t IsCapturing(hipStream_t, hipStreamCaptureStatus *s)
 void launch(const char *kernel, dim3 grid)
 {
     launches += " " + std::string(kernel) + ":" + std::to_string(grid.x);
+    grids.push_back(grid.x);
 }
 void reset()
 {
     launches.clear();
+    grids.clear();
     n_malloc = 0;
     malloc_status = sync_status = capture_query = hipSuccess;
     capture = hipStreamCaptureStatusNone;
@@ -78,11 +83,36 @@ static int louder()
     return 0;
 }
 
+static int slides()
+{
+    int T, F, n, y, sg;
+    if (std::scanf("%d %d %d", &T, &F, &n) != 3) return 2;
+    fake::reset();
+    stt_ctx c;
+    alignas(16) static float in[4];
+    std::vector<float *> Y, S;
+    std::vector<int32_t> shifts(n, 0);
+    for (int k = 0; k < n; ++k) {
+        if (std::scanf("%d %d", &y, &sg) != 2) return 2;
+        Y.push_back((float *)((uintptr_t)1 << 40) + ((size_t)y << 32));
+        S.push_back((float *)((uintptr_t)1 << 48) + ((size_t)sg << 32));
+    }
+    stt_spectro p{4096.0, 8192, 0, F, 4};
+    const stt_status st = stt_form_maps(&c, &p, T, in, in, in, in, n, shifts.data(), F, Y.data(), S.data());
+    const int per = 8 * ((T * F + 4095) / 4096);  // workgroups a slide takes, two bins per lane
+    std::printf("%d", st);
+    for (unsigned g : fake::grids) std::printf(" %u", g % per ? 0u : g / per);
+    std::printf("\n");
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
-    while (std::scanf("%15s", cmd) == 1)
-        if (std::strcmp(cmd, "louder") || louder()) return 2;
+    while (std::scanf("%15s", cmd) == 1) {
+        const int bad = !std::strcmp(cmd, "louder") ? louder() : !std::strcmp(cmd, "slides") ? slides() : 2;
+        if (bad) return bad;
+    }
     return 0;
 }
 

@@ -57,3 +57,20 @@ def test_counts_without_memory_are_direct(api):
 def test_counts_report_a_failed_stream(api):
     """The scratch waits for the stream before it moves; what the wait reports is the call's status."""
     assert api(f"louder 1000 10 64 0 0 {HIP_FAULT}") == [EHIP, "0", "message"]
+
+
+def _slides(api, pairs, T=1000, F=1000):
+    got = [int(x) for x in api(f"slides {T} {F} {len(pairs)} " + " ".join(f"{y} {s}" for y, s in pairs))]
+    assert got[0] == 0 and sum(got[1:]) == len(pairs)
+    return got[1:]
+
+
+def test_slides_of_one_launch_write_distinct_buffers(api):
+    """A launch writes its slides in no order, so slides into one buffer, of Y or of sigma, take launches of their
+    own: the last one stands, as the calls order them."""
+    own = [(k, k) for k in range(150)]
+    assert _slides(api, own) == [64, 64, 22]
+    assert _slides(api, [(0, 0), (0, 0), (1, 1), (2, 0), (2, 2), (3, 3)]) == [1, 2, 1, 2]
+    assert _slides(api, [(k, 7) for k in range(5)]) == [1] * 5        # one sigma for all
+    assert _slides(api, own[:64] + own[:64]) == [64, 64]              # the buffers of the launch before
+    assert _slides(api, own[:63] + own[:1] + own[63:80]) == [63, 18]

@@ -83,3 +83,21 @@ def test_slides_by_flat_bins(stt, ctx, T, F, pad, off, ns):
         assert (np.abs(s[:, :F] - ws) <= 1e-5 * ws).all()
         assert (y[:, F:] == canary).all() and (s[:, F:] == canary).all()
         assert bool((Ys[k][:off] == canary).all()) and bool((sg[k][:off] == canary).all())
+
+
+def test_last_slide_into_a_buffer_stands(stt, ctx):
+    """Slides given the same output maps are written in order (T F large enough that a slide's workgroups overlap
+    the next one's)."""
+    import torch
+    T, F, M = 400, 1000, 2048
+    print("repeated outputs", T, F, flush=True, file=sys.stderr)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    p = stt.Spectro(float(M), M, 3, F, 2)
+    si, sj = (torch.view_as_complex(torch.randn((T, F, 2), generator=g, device="cuda")) for _ in range(2))
+    pi, pj = (torch.rand((T, F), generator=g, device="cuda") + 0.5 for _ in range(2))
+    shifts = list(range(1, 41))
+    own = ctx.form_maps(p, si, pi, sj, pj, shifts)
+    a, b = ctx.form_maps(p, si, pi, sj, pj, [0, 0])
+    ctx.form_maps(p, si, pi, sj, pj, shifts, out=[a, b] * 20)
+    for got, want in ((a, own[38]), (b, own[39])):
+        assert torch.equal(got.Y, want.Y) and torch.equal(got.sigma, want.sigma)

@@ -31,7 +31,7 @@ struct stt_ctx {
     std::string err;
     void *scratch = nullptr;
     size_t scratch_bytes = 0;
-    void *aux = nullptr;  // top-K state and candidates
+    void *aux = nullptr;  // top-K state and candidates, packing's maximum, follow-up ranks
     size_t aux_bytes = 0;
     void *pbuf = nullptr;  // folded p = Y/sigma maps for LDS-DMA staging
     size_t pbuf_bytes = 0;
@@ -113,9 +113,16 @@ stt_status ensure_scratch(stt_ctx *c, size_t bytes)
     return STT_OK;
 }
 
+// What a top-K select needs of aux: its state and its candidates.
+constexpr size_t kTopkStateBytes = (sizeof(TopkState) + 255) & ~(size_t)255;
+constexpr size_t kTopkBytes = kTopkStateBytes + sizeof(uint64_t) * (size_t)kTopkCand;
+
+// At least a select's need at once: after any call that uses aux a select allocates nothing (it may be
+// recorded in a graph), and aux moves only for follow-ups of more maps than that holds ranks.
 stt_status ensure_aux(stt_ctx *c, size_t bytes)
 {
     if (bytes <= c->aux_bytes) return STT_OK;
+    bytes = std::max(bytes, kTopkBytes);
     if (c->aux) {
         hipError_t e = hipStreamSynchronize(c->stream);
         if (e != hipSuccess) return fail(c, STT_EHIP, "hipStreamSynchronize: %s", hipGetErrorString(e));
@@ -916,11 +923,10 @@ template <typename SRC>
 stt_status topk_launch(stt_ctx *c, SRC src, int64_t n, int64_t first, int32_t K, int last_only, int64_t *idx_dev,
                        float *val_dev)
 {
-    const size_t st_bytes = (sizeof(TopkState) + 255) & ~(size_t)255;
-    const stt_status s = ensure_aux(c, st_bytes + sizeof(uint64_t) * (size_t)kTopkCand);
+    const stt_status s = ensure_aux(c, kTopkBytes);
     if (s != STT_OK) return s;
     TopkState *st = (TopkState *)c->aux;
-    uint64_t *cand = (uint64_t *)((char *)c->aux + st_bytes);
+    uint64_t *cand = (uint64_t *)((char *)c->aux + kTopkStateBytes);
     // 8 elements per lane where that still fills the chip; each workgroup flushes a histogram
     const unsigned grid = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 2047) / 2048, 1024));
     hipLaunchKernelGGL(k_topk_init, dim3(kTopkPasses * kTopkBins / 1024), dim3(1024), 0, c->stream, st, (uint32_t)K);
@@ -1322,7 +1328,7 @@ stt_status stt_map_pack_p16(stt_ctx *c, const stt_map *map, void *out_dev, int64
     if (!out_dev || !scale_exp) return fail(c, STT_EINVAL, "out_dev and scale_exp must be non-NULL");
     if (out_ld < map->F) return fail(c, STT_EINVAL, "out_ld=%lld < F=%d", (long long)out_ld, map->F);
     STT_HIP(c, hipSetDevice(c->device));
-    if ((s = ensure_aux(c, sizeof(TopkState))) != STT_OK) return s;
+    if ((s = ensure_aux(c, sizeof(unsigned long long))) != STT_OK) return s;
     unsigned long long *amax = (unsigned long long *)c->aux;
     const MapP m = to_mapp(map);
     const int64_t n = (int64_t)map->T * map->F;

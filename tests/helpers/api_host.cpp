@@ -6,6 +6,8 @@
 //       statuses of hipMalloc and hipStreamSynchronize
 //   slides T F n (y s) x n -> status of stt_form_maps of n slides into buffers number y (Y) and s (sigma),
 //       F even, and the slides of each launch
+//   topk bytes n K cap -> after another call took `bytes` of the auxiliary scratch: status of stt_topk
+//       and its allocations, which fail while the stream captures (cap 1)
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -26,6 +28,7 @@ hipError_t Malloc(void **p, size_t bytes)
 {
     ++n_malloc;
     if (malloc_status != hipSuccess) return malloc_status;
+    if (capture != hipStreamCaptureStatusNone) return hipErrorStreamCaptureUnsupported;
     *p = std::malloc(bytes);
     return hipSuccess;
 }
@@ -106,11 +109,29 @@ static int slides()
     return 0;
 }
 
+static int topk()
+{
+    long long bytes, n;
+    int K, cap;
+    if (std::scanf("%lld %lld %d %d", &bytes, &n, &K, &cap) != 4) return 2;
+    fake::reset();
+    stt_ctx c;
+    if (bytes && ensure_aux(&c, (size_t)bytes) != STT_OK) return 2;
+    fake::n_malloc = 0;
+    fake::capture = cap ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    float z = 0.0f;
+    int64_t idx = 0;
+    const stt_status st = stt_topk(&c, &z, n, 0, K, &idx, &z);
+    std::printf("%d %d\n", st, fake::n_malloc);
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
     while (std::scanf("%15s", cmd) == 1) {
-        const int bad = !std::strcmp(cmd, "louder") ? louder() : !std::strcmp(cmd, "slides") ? slides() : 2;
+        const int bad = !std::strcmp(cmd, "louder") ? louder() : !std::strcmp(cmd, "slides") ? slides()
+                        : !std::strcmp(cmd, "topk") ? topk() : 2;
         if (bad) return bad;
     }
     return 0;

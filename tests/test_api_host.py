@@ -74,3 +74,11 @@ def test_slides_of_one_launch_write_distinct_buffers(api):
     assert _slides(api, [(k, 7) for k in range(5)]) == [1] * 5        # one sigma for all
     assert _slides(api, own[:64] + own[:64]) == [64, 64]              # the buffers of the launch before
     assert _slides(api, own[:63] + own[:1] + own[63:80]) == [63, 18]
+
+
+@pytest.mark.parametrize("bytes_before", [8, 1400, 50_000, 300_000])
+def test_captured_topk_after_any_other_call(api, bytes_before):
+    """The select and the other users of the auxiliary scratch (packing, follow-up ranks) share it: whichever comes
+    first, a select recorded later allocates nothing."""
+    assert api(f"topk {bytes_before} 5000 10 1") == ["0", "0"]
+    assert api("topk 0 5000 10 0") == ["0", "1"]

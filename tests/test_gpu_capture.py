@@ -44,3 +44,27 @@ def test_captured_counts_survive_scratch_growth():
                             tau_idx=None)
             s.synchronize()
     c.close()
+
+
+def test_topk_captured_after_packing():
+    """Packing is the first user of the scratch that a recorded select shares."""
+    import torch
+    import paper_1401_8060_amd.stt as stt
+    s = torch.cuda.Stream()
+    c = stt.Context(0, s)
+    with torch.cuda.stream(s):
+        c.pack_p16(stt.Map(*to_dev(*synth.noise_map(40, 32, seed=1))))
+        z = torch.randn(100_000, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            idx, val = c.topk(z, 100)
+        for rep in range(3):
+            print("captured select, replay", rep, flush=True, file=sys.stderr)
+            z.normal_()
+            graph.replay()
+            s.synchronize()
+            want = c.topk(z, 100)
+            assert torch.equal(idx, want[0]) and torch.equal(val, want[1])
+            assert val.tolist() == sorted(z.tolist(), reverse=True)[:100]
+    c.close()

@@ -141,8 +141,8 @@ stt_status stt_kernel_ms_total(stt_ctx *ctx, int32_t which, double *total_ms, in
  * (STT_EUNSUPPORTED when one column of the map does not fit lds_bytes), 3 =
  * one wave per template, direct gathers. All paths give bit-identical scores.
  * lds_bytes (0 = keep) is the slab budget per workgroup, in [1024, 163840];
- * default 163840. Until lds_bytes or a shape (stt_set_slab_shape, an autotuner)
- * has been set, calls choose both by their size. */
+ * default 163840. While it is the default and no shape has been set
+ * (stt_set_slab_shape, an autotuner), calls choose both by their size. */
 stt_status stt_set_path(stt_ctx *ctx, int32_t path, int32_t lds_bytes);
 
 /* Shape of the LDS-slab scorer: wg lanes per workgroup and tpt templates per

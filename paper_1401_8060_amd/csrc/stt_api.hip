@@ -25,6 +25,8 @@ struct Rec {
     bool used[3];
 };
 
+constexpr int kLdsBytes = 160 * 1024;  // LDS of a CU, the default slab budget
+
 struct stt_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -39,10 +41,10 @@ struct stt_ctx {
     size_t mdbuf_bytes = 0;
     bool dma = true;       // fold + double-buffered LDS-DMA staging where a column fits
     int path = 0;  // 0 auto, 1 direct, 2 slab
-    int lds_bytes = 160 * 1024;  // slab budget per workgroup
+    int lds_bytes = kLdsBytes;   // slab budget per workgroup
     int slab_wg = 1024;          // slab scorer shape: lanes per workgroup
     int slab_tpt = 4;            //                    templates per lane
-    bool auto_shape = true;      // shape and budget by the call's size, until the caller or a tuner sets either
+    bool shape_set = false;      // by the caller or a tuner; else, and with the default budget, calls choose by size
     bool hw_trig = true;         // hardware sine/cosine (measured max error 1.3e-7) or the polynomial
     // Timing: every call takes six events from a pool (start/end of the scoring
     // kernel, of the binning kernels and of the whole call); queries sum them.
@@ -568,12 +570,12 @@ stt_status bin_templates(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr
     return STT_OK;
 }
 
-// The shape of this call: the context's, or by size while neither shape nor budget has been set and
+// The shape of this call: the context's, or by size while no shape is set, the budget is the default and
 // the slabs stream in by DMA (registers stage into one buffer of the whole budget).
 SlabShape call_shape(const stt_ctx *c, int64_t n, int64_t col_bytes)
 {
     const SlabShape own{c->slab_wg, c->slab_tpt, c->lds_bytes};
-    if (!c->auto_shape || !c->dma) return own;
+    if (c->shape_set || c->lds_bytes != kLdsBytes || !c->dma) return own;
     const SlabShape sh = slab_shape_for(n, col_bytes);
     return aligned_slab(dma_slab_cols(sh.lds, col_bytes, 1)) >= 2 ? sh : own;
 }
@@ -1114,10 +1116,7 @@ stt_status stt_set_path(stt_ctx *c, int32_t path, int32_t lds_bytes)
     if (lds_bytes != 0 && (lds_bytes < 1024 || lds_bytes > 160 * 1024))
         return fail(c, STT_ERANGE, "lds_bytes=%d outside [1024, 163840]", lds_bytes);
     c->path = path;
-    if (lds_bytes) {
-        c->lds_bytes = lds_bytes;
-        c->auto_shape = false;
-    }
+    if (lds_bytes) c->lds_bytes = lds_bytes;
     return STT_OK;
 }
 
@@ -1127,7 +1126,7 @@ stt_status stt_set_slab_shape(stt_ctx *c, int32_t wg, int32_t tpt)
     if (!slab_shape_ok(wg, tpt)) return fail(c, STT_EUNSUPPORTED, "no slab scorer for %d x %d", wg, tpt);
     c->slab_wg = wg;
     c->slab_tpt = tpt;
-    c->auto_shape = false;
+    c->shape_set = true;
     return STT_OK;
 }
 
@@ -2107,8 +2106,8 @@ std::string tune_key_batch(const stt_ctx *c, int F, int dtype, int T, int n_maps
 stt_status tune_search(stt_ctx *c, int F, int reps, const std::function<stt_status()> &call, TuneChoice &best)
 {
     const int old_path = c->path, old_wg = c->slab_wg, old_tpt = c->slab_tpt, old_lds = c->lds_bytes;
-    const bool old_timing = c->timing, old_graph = c->use_graph, old_auto = c->auto_shape;
-    c->auto_shape = false;
+    const bool old_timing = c->timing, old_graph = c->use_graph, old_set = c->shape_set;
+    c->shape_set = true;
     std::vector<Rec> saved;
     saved.swap(c->recs);
     const size_t saved_next = c->next;
@@ -2146,7 +2145,7 @@ stt_status tune_search(stt_ctx *c, int F, int reps, const std::function<stt_stat
     c->lds_bytes = old_lds;
     c->timing = old_timing;
     c->use_graph = old_graph;
-    c->auto_shape = old_auto;
+    c->shape_set = old_set;
     c->recs.swap(saved);
     c->next = saved_next;
     if (s != STT_OK) return s;
@@ -2161,7 +2160,7 @@ stt_status apply_choice(stt_ctx *c, const std::string &key, const TuneChoice &be
     c->slab_wg = best.wg;
     c->slab_tpt = best.tpt;
     c->lds_bytes = best.lds;
-    c->auto_shape = false;
+    c->shape_set = true;
     if (choice_out) {
         choice_out[0] = best.wg;
         choice_out[1] = best.tpt;

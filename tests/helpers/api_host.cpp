@@ -8,6 +8,8 @@
 //       F even, and the slides of each launch
 //   topk bytes n K cap -> after another call took `bytes` of the auxiliary scratch: status of stt_topk
 //       and its allocations, which fail while the stream captures (cap 1)
+//   shape wg tpt lds ... - n col_bytes -> the slab shape of a call of n templates on columns of col_bytes, after
+//       stt_set_slab_shape(wg, tpt) (0 0: not called) and a stt_set_path for each lds (0: budget kept)
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -126,12 +128,29 @@ static int topk()
     return 0;
 }
 
+static int shape()
+{
+    int wg, tpt;
+    char w[32];
+    long long n, col;
+    if (std::scanf("%d %d", &wg, &tpt) != 2) return 2;
+    stt_ctx c;
+    if (wg && stt_set_slab_shape(&c, wg, tpt) != STT_OK) return 2;
+    while (std::scanf("%31s", w) == 1 && std::strcmp(w, "-"))
+        if (stt_set_path(&c, 0, std::atoi(w)) != STT_OK) return 2;
+    if (std::scanf("%lld %lld", &n, &col) != 2) return 2;
+    const SlabShape sh = call_shape(&c, n, col);
+    std::printf("%d %d %d\n", sh.wg, sh.tpt, sh.lds);
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
     while (std::scanf("%15s", cmd) == 1) {
         const int bad = !std::strcmp(cmd, "louder") ? louder() : !std::strcmp(cmd, "slides") ? slides()
-                        : !std::strcmp(cmd, "topk") ? topk() : 2;
+                        : !std::strcmp(cmd, "topk") ? topk()
+                        : !std::strcmp(cmd, "shape") ? shape() : 2;
         if (bad) return bad;
     }
     return 0;

@@ -82,3 +82,20 @@ def test_captured_topk_after_any_other_call(api, bytes_before):
     first, a select recorded later allocates nothing."""
     assert api(f"topk {bytes_before} 5000 10 1") == ["0", "0"]
     assert api("topk 0 5000 10 0") == ["0", "1"]
+
+
+K160, K80 = 160 * 1024, 80 * 1024
+
+
+def test_default_budget_leaves_the_shape_to_the_calls(api):
+    """lds_bytes = 163840 is the documented default: setting it, alone or after another budget, is the context as it
+    was created. A shape that was set stays."""
+    def shape(sets, wg=0, tpt=0):
+        return [int(x) for x in api(f"shape {wg} {tpt} {' '.join(map(str, sets))} - 10000000 8192")]
+    free = shape([])
+    assert free == [1024, 2, K80]
+    assert shape([0]) == free and shape([K160]) == free
+    assert shape([48 * 1024]) == [1024, 4, 48 * 1024]
+    assert shape([48 * 1024, 0]) == [1024, 4, 48 * 1024]
+    assert shape([48 * 1024, K160]) == free
+    assert shape([K160], 1024, 4) == [1024, 4, K160] and shape([K80, K160], 512, 2) == [512, 2, K160]

@@ -1644,10 +1644,10 @@ stt_status stt_score_batch(stt_ctx *c, const stt_map *maps_host, int32_t n_maps,
     const int esize = fold_esize(dtype);
     std::vector<BatchMap> bm(n_maps);
     std::vector<uint32_t> chunk_start(n_maps + 1), item_start(n_maps + 1), fine_start(n_maps + 1);
-    // one shape for the batch, by its total templates and widest column
+    // one shape for the batch, by its total templates and widest column (what is out of range is refused below)
     int64_t n_total = 0, widest = 0;
     for (int i = 0; i < n_maps; ++i) {
-        n_total += std::max<int64_t>(0, n_trk_host[i]);
+        n_total += std::clamp<int64_t>(n_trk_host[i], 0, (int64_t)1 << 32);
         widest = std::max(widest, fold_ld(std::max(1, maps_host[i].F), esize) * esize);
     }
     const SlabShape sh = call_shape(c, n_total, widest);

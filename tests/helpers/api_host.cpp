@@ -10,6 +10,7 @@
 //       and its allocations, which fail while the stream captures (cap 1)
 //   shape wg tpt lds ... - n col_bytes -> the slab shape of a call of n templates on columns of col_bytes, after
 //       stt_set_slab_shape(wg, tpt) (0 0: not called) and a stt_set_path for each lds (0: budget kept)
+//   batch n0 n1 -> status of stt_score_batch for two maps of these many templates
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -144,13 +145,37 @@ static int shape()
     return 0;
 }
 
+static int batch()
+{
+    long long n0, n1;
+    if (std::scanf("%lld %lld", &n0, &n1) != 2) return 2;
+    fake::reset();
+    stt_ctx c;
+    float y[2], sg = 1.0f;
+    stt_map m{};
+    m.Y = y;
+    m.sigma = &sg;
+    m.T = 100;
+    m.F = 64;
+    m.ld = 64;
+    m.dtype = STT_C64F32;
+    const stt_map maps[2] = {m, m};
+    const int64_t n[2] = {n0, n1};
+    stt_gen g{};
+    g.min_len = 10;
+    uint64_t best[2] = {};
+    std::printf("%d\n", stt_score_batch(&c, maps, 2, &g, n, STT_NORM_N, best, nullptr));
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
     while (std::scanf("%15s", cmd) == 1) {
         const int bad = !std::strcmp(cmd, "louder") ? louder() : !std::strcmp(cmd, "slides") ? slides()
                         : !std::strcmp(cmd, "topk") ? topk()
-                        : !std::strcmp(cmd, "shape") ? shape() : 2;
+                        : !std::strcmp(cmd, "shape") ? shape()
+                        : !std::strcmp(cmd, "batch") ? batch() : 2;
         if (bad) return bad;
     }
     return 0;

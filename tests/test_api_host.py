@@ -20,7 +20,9 @@ def api(tmp_path_factory):
         pytest.skip("hipcc not available")
     out = tmp_path_factory.mktemp("api") / "api"
     subprocess.run([hipcc, "--cuda-host-only", "-O1", "-std=c++17", "-x", "hip", "--offload-arch=gfx950", "-w",
-                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1401_8060_amd", "csrc"),
+                    "-Xarch_host", "-fsanitize=signed-integer-overflow", "-Xarch_host",
+                    "-fsanitize-trap=signed-integer-overflow", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_1401_8060_amd", "csrc"),
                     os.path.join(ROOT, "tests", "helpers", "api_host.cpp"), "-o", str(out)],
                    check=True, capture_output=True)
 
@@ -99,3 +101,10 @@ def test_default_budget_leaves_the_shape_to_the_calls(api):
     assert shape([48 * 1024, 0]) == [1024, 4, 48 * 1024]
     assert shape([48 * 1024, K160]) == free
     assert shape([K160], 1024, 4) == [1024, 4, K160] and shape([K80, K160], 512, 2) == [512, 2, K160]
+
+
+@pytest.mark.parametrize("n0,n1", [(2**63 - 1, 2**63 - 1), (2**62, 2**62), (100, 2**32 + 1), (-1, 2**63 - 1)])
+def test_batch_counts_are_refused_without_overflow(api, n0, n1):
+    """Counts out of range are summed for the shape before they are refused (this build traps where a signed sum
+    overflows)."""
+    assert api(f"batch {n0} {n1}") == ["-2"]

@@ -1782,6 +1782,15 @@ __global__ __launch_bounds__(kWG) void k_score_md_direct(MapP m, GenP g, const T
     if (last) merge_key(best, key);
 }
 
+// Between a wave's LDS stores and its lanes' loads of each other's values (or the other way round). The
+// LDS serves a wave in order; the fences keep the compiler to that order and cost no instruction.
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // One wave per template for small calls: lanes over flush groups as k_score_wave, each group's kMD
 // partial sums through LDS to kMD lanes, which add them in column order (the same bits as the other
 // scorers). Four waves per workgroup, which strides over the templates.
@@ -1811,10 +1820,10 @@ __global__ __launch_bounds__(256) void k_score_md_wave(MapP m, GenP g, const Trk
 #pragma unroll
                     for (int q = 0; q < kMD; ++q) gs[lane][q] = part[q];
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
                 if (lane < kMD)
                     for (int l = 0; l < min(64, glast - r0 + 1); ++l) acc += gs[l][lane];
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
             }
             const int32_t N = t.t2 - t.t0 + 1;
             const float v = lane < dg.cnt ? finish(acc, N, norm, m.scale) : -__builtin_inff();

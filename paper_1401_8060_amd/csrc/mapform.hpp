@@ -21,7 +21,7 @@ namespace stt {
 constexpr int kFftThreads = 256;   // at most; a column of N points uses N / 8
 constexpr int kMaxFftM = 8192;     // samples per column; the complex FFT has M/2 points in LDS
 constexpr int kSlidesPerLaunch = 64;  // 20 bytes each of the 4 KB of kernel arguments
-constexpr int kPsdCols = 4;        // columns per lane of k_psd
+constexpr int64_t kPsdPixels = (int64_t)2 << 20;  // T F from which k_psd takes four columns per lane
 
 struct SlideArgs {
     float2 *Y[kSlidesPerLaunch];
@@ -135,30 +135,49 @@ __global__ __launch_bounds__(kFftThreads) void k_col_fft(const float *__restrict
     }
 }
 
+// |s~|^2 as every size sums it: the contraction is written out, and sums add it as it is.
+__device__ __forceinline__ float power(float2 v)
+{
+#pragma clang fp contract(off)
+    return __builtin_fmaf(v.x, v.x, v.y * v.y);
+}
+
 // P'(t; f) = scale * mean |spec(t', f)|^2 over 2 <= |t' - t| <= nb + 1 inside [0, T).
-// Grid: (ceil(F / 256), ceil(T / kPsdCols)); every column has a neighbour (T >= 4, checked by the
-// host). A lane sums kPsdCols columns, each neighbour read once for all of them (3.5 reads per column
-// instead of 8 at nb = 4); every sum runs over t' in ascending order.
+// Grid: (ceil(F / 256), ceil(T / C)); every column has a neighbour (T >= 4, checked by the host). A
+// lane sums C columns, and every sum runs over t' in ascending order, so C changes no bit.
+// Spectra that stay in the L2s are bound by latency: one column per lane, its neighbours in flight
+// together (us for C = 1 and 4 at nb = 4: 2.3 and 3.0 at 100 x 60, 3.9 and 4.5 at 500 x 800, 5.9 and
+// 6.4 at 1000 x 1000). Larger ones are bound by the reads: four columns read each neighbour once for
+// all of them, 3.5 reads per column instead of 8 (13.7 and 14.2 at 1500 x 2000, 23.7 and 19.4 with
+// nb = 8; 24.2 and 19.7 at 1500 x 2660, 35.2 and 24.8 at 1500 x 3840).
+template <int C>
 __global__ __launch_bounds__(256) void k_psd(const float2 *__restrict__ spec, int T, int F, int nb, float scale,
                                              float *__restrict__ psd)
 {
+#pragma clang fp contract(off)
     const int f = blockIdx.x * 256 + threadIdx.x;
-    const int t0 = blockIdx.y * kPsdCols;
+    const int t0 = blockIdx.y * C;
     if (f >= F) return;
-    float acc[kPsdCols] = {};
-    const int lo = max(t0 - nb - 1, 0), hi = min(t0 + kPsdCols + nb, T - 1);
+    float acc[C] = {};
+    const int lo = max(t0 - nb - 1, 0), hi = min(t0 + C + nb, T - 1);
+    if constexpr (C == 1) {
 #pragma unroll 4
-    for (int u = lo; u <= hi; ++u) {
-        const float2 v = spec[(int64_t)u * F + f];
-        const float q = v.x * v.x + v.y * v.y;
+        for (int u = lo; u <= t0 - 2; ++u) acc[0] += power(spec[(int64_t)u * F + f]);
+#pragma unroll 4
+        for (int u = t0 + 2; u <= hi; ++u) acc[0] += power(spec[(int64_t)u * F + f]);
+    } else {
+#pragma unroll 4
+        for (int u = lo; u <= hi; ++u) {
+            const float q = power(spec[(int64_t)u * F + f]);
 #pragma unroll
-        for (int j = 0; j < kPsdCols; ++j) {
-            const int d = u > t0 + j ? u - t0 - j : t0 + j - u;
-            if (d >= 2 && d <= nb + 1) acc[j] += q;
+            for (int j = 0; j < C; ++j) {
+                const int d = u > t0 + j ? u - t0 - j : t0 + j - u;
+                if (d >= 2 && d <= nb + 1) acc[j] += q;
+            }
         }
     }
 #pragma unroll
-    for (int j = 0; j < kPsdCols; ++j) {
+    for (int j = 0; j < C; ++j) {
         const int t = t0 + j;
         if (t >= T) break;
         const int cnt = max(0, min(nb, t - 1)) + max(0, min(nb, T - 2 - t));

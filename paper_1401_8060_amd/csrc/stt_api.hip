@@ -1493,13 +1493,19 @@ stt_status stt_spectra(stt_ctx *c, const stt_spectro *p, const float *strain_dev
     while ((1 << lg) < N) ++lg;
     ev_record(c, 4);
     // a lane holds 8 points at a time. 1000 columns of 4096 samples: 28 us a stage at a time through LDS,
-    // 15 us with three stages in registers; the power sums 11 and 7.5 us (a column, four columns a lane).
+    // 15 us with three stages in registers.
     const int fft_wg = std::min(kFftThreads, std::max(64, N / 8));
     hipLaunchKernelGGL(k_col_fft, dim3(T), dim3(fft_wg), sizeof(float2) * fft_slot(N), c->stream, strain_dev, p->M, lg,
                        p->k_lo, p->F, (float)(1.0 / p->fs), (const float2 *)c->fft_tab, (float2 *)spec_dev);
     STT_HIP(c, hipGetLastError());
-    hipLaunchKernelGGL(k_psd, dim3((p->F + 255) / 256, (T + kPsdCols - 1) / kPsdCols), dim3(256), 0, c->stream,
-                       (const float2 *)spec_dev, T, p->F, std::min(p->nb, T), cross_scale(p), psd_dev);
+    const int psd_cols = (int64_t)T * p->F >= kPsdPixels ? 4 : 1;
+    const dim3 psd_grid((p->F + 255) / 256, (T + psd_cols - 1) / psd_cols);
+    if (psd_cols == 4)
+        hipLaunchKernelGGL(k_psd<4>, psd_grid, dim3(256), 0, c->stream, (const float2 *)spec_dev, T, p->F,
+                           std::min(p->nb, T), cross_scale(p), psd_dev);
+    else
+        hipLaunchKernelGGL(k_psd<1>, psd_grid, dim3(256), 0, c->stream, (const float2 *)spec_dev, T, p->F,
+                           std::min(p->nb, T), cross_scale(p), psd_dev);
     STT_HIP(c, hipGetLastError());
     ev_record(c, 5);
     c->used[2] = true;

@@ -101,3 +101,17 @@ def test_last_slide_into_a_buffer_stands(stt, ctx):
     ctx.form_maps(p, si, pi, sj, pj, shifts, out=[a, b] * 20)
     for got, want in ((a, own[38]), (b, own[39])):
         assert torch.equal(got.Y, want.Y) and torch.equal(got.sigma, want.sigma)
+
+
+@pytest.mark.parametrize("T,nb", [(600, 4), (601, 1), (602, 9), (603, 700)])
+def test_power_sums_on_both_sides_of_their_rule(stt, ctx, T, nb):
+    """One column per lane below T F = 2^21, four from there on: P' of the bins that both calls hold are the same
+    bits."""
+    import torch
+    M, F = 8192, (1 << 21) // T
+    print("power sums", T, F, nb, flush=True, file=sys.stderr)
+    x = torch.randn((T + 1) * M // 2, generator=torch.Generator(device="cuda").manual_seed(T), device="cuda")
+    assert T * F < 1 << 21 <= T * (F + 1)
+    spec, psd = ctx.spectra(x, stt.Spectro(4096.0, M, 3, F, nb), T)
+    spec4, psd4 = ctx.spectra(x, stt.Spectro(4096.0, M, 3, F + 1, nb), T)
+    assert torch.equal(spec, spec4[:, :F]) and torch.equal(psd, psd4[:, :F])

@@ -185,6 +185,22 @@ __global__ __launch_bounds__(256) void k_psd(const float2 *__restrict__ spec, in
     }
 }
 
+// Order of an XCD's workgroups over the n slides of a launch, `per` of them per slide: runs of
+// kFormRun bins (`run` workgroups), every slide's part of a run before the next run. Workgroup b of
+// the XCD takes place `at` of its part of slide k.
+struct SlideItem {
+    uint32_t k, at;
+};
+constexpr uint32_t kFormRun = 131072;
+
+__host__ __device__ __forceinline__ SlideItem slide_item(uint32_t b, uint32_t per, uint32_t n, uint32_t run)
+{
+    run = run < per ? run : per;
+    const uint32_t base = b / (run * n) * run, size = run < per - base ? run : per - base;
+    const uint32_t rem = b - base * n, k = rem / size;
+    return {k, base + rem - k * size};
+}
+
 // One launch writes up to kSlidesPerLaunch slide maps, one after the other: a workgroup takes 256 P
 // consecutive bins of one slide (rows of F bins end to end; P = 2 when F and ld are even and the
 // buffers 16-byte aligned: one 16-byte and one 8-byte store per lane), so that the workgroups in
@@ -192,10 +208,17 @@ __global__ __launch_bounds__(256) void k_psd(const float2 *__restrict__ spec, in
 // fill: 256 maps of 1000 x 1000 in 448 us, 6.9 TB/s of the card's 6.9. A workgroup that wrote its
 // bins to 16 maps in turn scattered the stores over 16 maps at once (915 us; past the caches 765);
 // two slides per workgroup take 511 us, stores through the caches 723. Workgroups go round-robin to
-// the 8 XCDs; the remap gives each XCD one contiguous run of bins of every slide, so its I columns,
-// and for neighbouring shifts its J columns, stay in its own L2 (shifts in random order: 677 us).
+// the 8 XCDs; the remap gives each XCD one contiguous part of every slide, so its I columns, and for
+// neighbouring shifts its J columns, stay in its own L2 (shifts in random order: 677 us). 131072 bins
+// of both spectra are 3 MB of an L2's 4: a part larger than that is written in runs of so many bins,
+// all slides of a run before the next run. Slide by slide, larger spectra come from beyond the L2s
+// for every slide again (1500 x 2000, 4 slides: 51 us, in runs 29; 1500 x 3840: 96 and 57, 16 slides
+// 376 and 184; runs of 262144 bins 44, 95 and 364, of 65536 28, 57 and 191).
+// Stores past the caches leave the maps in memory: one 1000 x 1000 map and a reading pass over it take
+// 10.9 us, 10.5 with stores through the caches, 8 maps 50.2 and 51.8, 4 of 1500 x 2000 62.2 and 66.0.
 // Grid: 1-D, 8 * ceil(nchunk / 8) * a.n workgroups of 256 lanes, nchunk = ceil(T F / (256 P)).
-template <int P>
+// RUNS: parts larger than a run (the order's divisions cost 256 maps of 1000 x 1000 4 us of 448).
+template <int P, bool RUNS>
 __global__ __launch_bounds__(256) void k_form_maps(const float2 *__restrict__ si, const float *__restrict__ pi,
                                                    const float2 *__restrict__ sj, const float *__restrict__ pj,
                                                    int T, int F, float scale, int64_t ld, SlideArgs a)
@@ -203,8 +226,15 @@ __global__ __launch_bounds__(256) void k_form_maps(const float2 *__restrict__ si
     const uint32_t n = (uint32_t)T * (uint32_t)F;  // < 2^29 (T < 2^16, F <= kMaxFftM / 2)
     const uint32_t nchunk = (n + 256 * P - 1) / (256 * P);
     const uint32_t per = (nchunk + 7) / 8;
-    const uint32_t b = blockIdx.x / 8, k = b / per;
-    const uint32_t L = (blockIdx.x % 8) * per + (b - k * per);
+    const uint32_t b = blockIdx.x / 8;
+    SlideItem w;
+    if constexpr (RUNS) {
+        w = slide_item(b, per, (uint32_t)a.n, kFormRun / (256 * P));
+    } else {
+        w.k = b / per;
+        w.at = b - w.k * per;
+    }
+    const uint32_t k = w.k, L = (blockIdx.x % 8) * per + w.at;
     if (L >= nchunk) return;
     const uint32_t i = P * (L * 256 + threadIdx.x);
     if (i >= n) return;

@@ -1546,6 +1546,9 @@ stt_status stt_form_maps(stt_ctx *c, const stt_spectro *p, int32_t T, const floa
     // a launch holds below 2^32 lanes: at least 15 slides of the largest map
     const int64_t slide_wgs = 8 * ((nchunk + 7) / 8);
     const int per_launch = (int)std::min<int64_t>(kSlidesPerLaunch, (((int64_t)1 << 24) - 1) / slide_wgs);
+    const bool runs = slide_wgs / 8 > kFormRun / (256 * per_lane);
+    auto kern = pair ? (runs ? k_form_maps<2, true> : k_form_maps<2, false>)
+                     : (runs ? k_form_maps<1, true> : k_form_maps<1, false>);
     // a launch writes its slides in no order: a buffer that comes again starts the next launch, so that
     // the last slide into it stands
     const auto taken = [](const SlideArgs &a, const float *Y, const float *sigma) {
@@ -1562,12 +1565,8 @@ stt_status stt_form_maps(stt_ctx *c, const stt_spectro *p, int32_t T, const floa
             a.shift[a.n] = (int32_t)(sh < 0 ? sh + T : sh);
         }
         const dim3 grid((unsigned)(slide_wgs * a.n));
-        if (pair)
-            hipLaunchKernelGGL(k_form_maps<2>, grid, dim3(256), 0, c->stream, (const float2 *)spec_i_dev, psd_i_dev,
-                               (const float2 *)spec_j_dev, psd_j_dev, T, p->F, cross_scale(p), ld, a);
-        else
-            hipLaunchKernelGGL(k_form_maps<1>, grid, dim3(256), 0, c->stream, (const float2 *)spec_i_dev, psd_i_dev,
-                               (const float2 *)spec_j_dev, psd_j_dev, T, p->F, cross_scale(p), ld, a);
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, c->stream, (const float2 *)spec_i_dev, psd_i_dev,
+                           (const float2 *)spec_j_dev, psd_j_dev, T, p->F, cross_scale(p), ld, a);
         STT_HIP(c, hipGetLastError());
     }
     ev_record(c, 1);

@@ -11,6 +11,7 @@
 //   shape wg tpt lds ... - n col_bytes -> the slab shape of a call of n templates on columns of col_bytes, after
 //       stt_set_slab_shape(wg, tpt) (0 0: not called) and a stt_set_path for each lds (0: budget kept)
 //   batch n0 n1 -> status of stt_score_batch for two maps of these many templates
+//   items per n run -> (slide, place) of the per n workgroups that an XCD takes of a slide launch, in order
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -168,6 +169,18 @@ static int batch()
     return 0;
 }
 
+static int items()
+{
+    unsigned per, n, run;
+    if (std::scanf("%u %u %u", &per, &n, &run) != 3) return 2;
+    for (unsigned b = 0; b < per * n; ++b) {
+        const SlideItem w = slide_item(b, per, n, run);
+        std::printf("%u %u ", w.k, w.at);
+    }
+    std::printf("\n");
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -175,7 +188,8 @@ int main()
         const int bad = !std::strcmp(cmd, "louder") ? louder() : !std::strcmp(cmd, "slides") ? slides()
                         : !std::strcmp(cmd, "topk") ? topk()
                         : !std::strcmp(cmd, "shape") ? shape()
-                        : !std::strcmp(cmd, "batch") ? batch() : 2;
+                        : !std::strcmp(cmd, "batch") ? batch()
+                        : !std::strcmp(cmd, "items") ? items() : 2;
         if (bad) return bad;
     }
     return 0;

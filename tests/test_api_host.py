@@ -108,3 +108,12 @@ def test_batch_counts_are_refused_without_overflow(api, n0, n1):
     """Counts out of range are summed for the shape before they are refused (this build traps where a signed sum
     overflows)."""
     assert api(f"batch {n0} {n1}") == ["-2"]
+
+
+@pytest.mark.parametrize("per,n,run", [(1, 1, 256), (245, 3, 256), (256, 2, 256), (257, 2, 256), (700, 5, 256), (513, 1, 512),
+                                       (1025, 64, 512)])
+def test_slide_workgroups_in_runs(api, per, n, run):
+    """Each workgroup of each slide once: run by run of the XCD's part, slide by slide within a run, front to back."""
+    got = [int(x) for x in api(f"items {per} {n} {run}")]
+    want = [(k, at) for r in range(0, per, run) for k in range(n) for at in range(r, min(r + run, per))]
+    assert list(zip(got[::2], got[1::2])) == want

@@ -115,3 +115,21 @@ def test_power_sums_on_both_sides_of_their_rule(stt, ctx, T, nb):
     spec, psd = ctx.spectra(x, stt.Spectro(4096.0, M, 3, F, nb), T)
     spec4, psd4 = ctx.spectra(x, stt.Spectro(4096.0, M, 3, F + 1, nb), T)
     assert torch.equal(spec, spec4[:, :F]) and torch.equal(psd, psd4[:, :F])
+
+
+@pytest.mark.parametrize("T,F,pad", [(1049, 1000, 0), (700, 1501, 0), (530, 2000, 6)])
+def test_slides_in_runs(stt, ctx, T, F, pad):
+    """Maps of more than 8 runs of 131072 bins: each slide equals the map of a call of its own, and the map of the
+    circularly shifted spectra (both bins per lane, one, padded rows)."""
+    import torch
+    print("slides in runs", T, F, pad, flush=True, file=sys.stderr)
+    g = torch.Generator(device="cuda").manual_seed(F)
+    p = stt.Spectro(4096.0, 8192, 3, F, 2)
+    si, sj = (torch.view_as_complex(torch.randn((T, F, 2), generator=g, device="cuda")) for _ in range(2))
+    pi, pj = (torch.rand((T, F), generator=g, device="cuda") + 0.5 for _ in range(2))
+    shifts = [0, 3, -5, T - 1, 400]
+    maps = ctx.form_maps(p, si, pi, sj, pj, shifts, ld=F + pad)
+    for sh, m in zip(shifts, maps):
+        for args in ((sj, pj, sh), (sj.roll(-sh, 0).contiguous(), pj.roll(-sh, 0).contiguous(), 0)):
+            (one,) = ctx.form_maps(p, si, pi, *args[:2], [args[2]])
+            assert torch.equal(m.Y, one.Y) and torch.equal(m.sigma, one.sigma)

@@ -2486,18 +2486,47 @@ __device__ __forceinline__ void smooth_node(float2 p, const RowPhase &h, float &
     gd = h.w * (h.s * p.x + h.c * p.y);
 }
 
-// p of two neighbouring rows of one column.
+// p of rows r and r + 1 of two neighbouring columns, element e = (i, r) of the map: p[column][row].
+// A lane's second column is its neighbour's first, and a wave's loads of one column fill up to 64
+// cache lines of Y and 64 of sigma. The four loads of an FP32 map go out back to back, by array:
+// with address arithmetic or the other array's load in between, the lines of the first column have
+// left the L1 when the second one asks for them (20 000 templates on 1000 x 1000, 1000 samples each:
+// 269 us, back to back 225; 500 samples 224 and 208).
 template <int MAPT>
-__device__ __forceinline__ void load_p2(const MapP &m, int64_t e, float2 &p0, float2 &p1)
+__device__ __forceinline__ void load_p22(const MapP &m, int64_t e, float2 (&p)[2][2])
 {
-    if constexpr (MAPT == kMapPF) {
-        typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
-        const f4 v = *reinterpret_cast<const f4 *>(m.Y + e);
-        p0 = make_float2(v.x, v.y);
-        p1 = make_float2(v.z, v.w);
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(8)));
+    if constexpr (MAPT == kMapF32) {
+        typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+        typedef const __attribute__((address_space(1))) f4 *g4;
+        typedef const __attribute__((address_space(1))) f2 *g2;
+        uint64_t s0 = (uint64_t)(m.sig + e), s1 = (uint64_t)(m.sig + e + m.ld);
+        uint64_t y0 = (uint64_t)(m.Y + e), y1 = (uint64_t)(m.Y + e + m.ld);
+        asm volatile("" : "+v"(s0), "+v"(s1), "+v"(y0), "+v"(y1));  // all addresses before the first load
+        __builtin_amdgcn_sched_barrier(0);
+        const f2 s[2] = {*(g2)s0, *(g2)s1};
+        __builtin_amdgcn_sched_barrier(0);
+        const f4 y[2] = {*(g4)y0, *(g4)y1};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float w0 = 1.0f / s[c].x, w1 = 1.0f / s[c].y;
+            p[c][0] = make_float2(y[c].x * w0, y[c].y * w0);
+            p[c][1] = make_float2(y[c].z * w1, y[c].w * w1);
+        }
+    } else if constexpr (MAPT == kMapPF) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const f4 v = *reinterpret_cast<const f4 *>(m.Y + e + c * m.ld);
+            p[c][0] = make_float2(v.x, v.y);
+            p[c][1] = make_float2(v.z, v.w);
+        }
     } else {
-        p0 = load_p<MAPT>(m, e);
-        p1 = load_p<MAPT>(m, e + 1);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            p[c][0] = load_p<MAPT>(m, e + c * m.ld);
+            p[c][1] = load_p<MAPT>(m, e + c * m.ld + 1);
+        }
     }
 }
 
@@ -2548,16 +2577,14 @@ __device__ __forceinline__ void smooth_block(const MapP &m, const float *th, int
         const bool ut = u0 >= 0.0 && u0 <= (double)(m.T - 1), vt = v0 >= 0.0 && v0 <= (double)(m.F - 1);
         const int i = min((int)floor(u), m.T - 2), r = min((int)floor(v), m.F - 2);
         const double a = u - (double)i, b = v - (double)r;
-        const int64_t e = i * m.ld + r;
-        float2 p00, p01, p10, p11;
-        load_p2<MAPT>(m, e, p00, p01);
-        load_p2<MAPT>(m, e + m.ld, p10, p11);
+        float2 p[2][2];
+        load_p22<MAPT>(m, i * m.ld + r, p);
         const RowPhase h0 = row_phase(m, r, dtau_s), h1 = row_phase(m, r + 1, dtau_s);
         float G00, G10, G01, G11, D00, D10, D01, D11;
-        smooth_node(p00, h0, G00, D00);
-        smooth_node(p10, h0, G10, D10);
-        smooth_node(p01, h1, G01, D01);
-        smooth_node(p11, h1, G11, D11);
+        smooth_node(p[0][0], h0, G00, D00);
+        smooth_node(p[1][0], h0, G10, D10);
+        smooth_node(p[0][1], h1, G01, D01);
+        smooth_node(p[1][1], h1, G11, D11);
         const double w00 = (1 - a) * (1 - b), w10 = a * (1 - b), w01 = (1 - a) * b, w11 = a * b;
         sum[0] += w00 * G00 + w10 * G10 + w01 * G01 + w11 * G11;
         const double du = ut ? (1 - b) * (G10 - G00) + b * (G11 - G01) : 0.0;

@@ -47,14 +47,13 @@ __global__ __launch_bounds__(256) void k_count_louder(const uint64_t *__restrict
 }
 
 // Counts over many reference keys. The direct count above walks them in one workgroup per 256
-// queries (about 17 ns per reference whatever the number of queries: 17.5 ms for 10^6), so from
-// kLouderDirect references on the queries are sorted in tiles (k_rank_sort), every reference finds
+// queries (17 ns per reference whatever the number of queries up to 10^5: 17.5 ms for 10^6), so where
+// that takes longer (prefer_ranks) the queries are sorted in tiles (k_rank_sort), every reference finds
 // its place among a tile's queries by bisection in LDS (k_rank_count), and the place histogram's
 // suffix sums are the counts (k_rank_finish): 10^6 references and 1000 queries in 36 us (sort 16, count 15,
 // sums 5).
 constexpr int kRankTile = 4096;       // queries per tile
 constexpr int kRankTiles = 64;        // tiles per pass
-constexpr int kLouderDirect = 512;    // references up to which the direct count is the faster one
 
 struct RankTile {
     uint32_t hi[kRankTile];                // sorted high words

@@ -951,8 +951,27 @@ bool capturing(stt_ctx *c)
     return true;
 }
 
-// Counts (and FAP = count / n_ref) of n_q query keys against n_ref reference keys: directly up to
-// kLouderDirect references, else by ranks in passes of kRankTiles tiles of queries. The ranks need
+// Whether counts go by ranks. Directly they take 17 ns per reference, from 180 000 queries on more (25 ns
+// for 3 x 10^5, 60 for 10^6); by ranks, a pass takes 12 us and, for the sort of its tiles, 11 ns per place
+// of a tile (a power of two), and hardly depends on the references up to 10^4. Measured (us, direct and
+// ranks): 513 references 10 and 12 for one query, 11 and 56 for 10^5; 1000 references 18 and 13 for one
+// query, 19 and 25 for 1000, 19 and 55 for 4096; 2000 references 36 and 25 for 1000, 36 and 34 for 2048;
+// 3000 references 53 and 58 for 4096; 5000 references 87 and 64 for 4096, 129 and 133 for 3 x 10^5.
+bool prefer_ranks(int64_t n_ref, int64_t n_q)
+{
+    const int64_t per_pass = (int64_t)kRankTile * kRankTiles;
+    const auto pass_ns = [](int64_t queries) {
+        int P = 64;
+        while (P < queries && P < kRankTile) P <<= 1;
+        return 11500.0 + 11.0 * P;
+    };
+    const int64_t full = n_q / per_pass, rest = n_q - full * per_pass;
+    return (double)n_ref * std::max(17.0, 8.0 + (double)n_q / 20000) >
+           (double)full * pass_ns(per_pass) + (rest ? pass_ns(rest) : 0.0);
+}
+
+// Counts (and FAP = count / n_ref) of n_q query keys against n_ref reference keys: directly, or by ranks
+// in passes of kRankTiles tiles of queries where those are faster. The ranks need
 // scratch. A call that finds no memory for it counts directly too, and so does one on a capturing stream: its
 // graph would keep the scratch's address, and the scratch moves when a later call needs more of it.
 stt_status count_louder(stt_ctx *c, const uint64_t *ref, int64_t n_ref, const uint64_t *q, int64_t n_q, int64_t *count,
@@ -960,7 +979,7 @@ stt_status count_louder(stt_ctx *c, const uint64_t *ref, int64_t n_ref, const ui
 {
     const int64_t per_pass = (int64_t)kRankTile * kRankTiles;
     const size_t need = sizeof(RankTile) * (size_t)std::min<int64_t>(kRankTiles, (n_q + kRankTile - 1) / kRankTile);
-    bool ranks = n_ref > kLouderDirect && !capturing(c);
+    bool ranks = prefer_ranks(n_ref, n_q) && !capturing(c);
     if (ranks) {
         const std::string before = c->err;
         const stt_status s = ensure_mdbuf(c, need);

@@ -32,10 +32,15 @@ def api(tmp_path_factory):
     return run
 
 
-def test_counts_take_ranks_above_the_direct_limit(api):
-    assert api("louder 512 10 0 0 0 0") == ["0", "0", *DIRECT]
-    assert api("louder 513 10 0 0 0 0") == ["0", "1", *RANKS]
-    assert api("louder 513 10 9999999 0 0 0") == ["0", "0", *RANKS]
+@pytest.mark.parametrize("n_q,direct,ranks", [(1, 717, 718), (65, 759, 760), (1000, 1339, 1340), (4096, 3326, 3327),
+                                              (100_000, 3326, 3327), (262_145, 3257, 3258), (1_000_000, 3900, 3901)])
+def test_counts_take_ranks_where_they_are_faster(api, n_q, direct, ranks):
+    """Both sides of the rule: references, for a number of queries, at which the sort of the queries pays."""
+    assert all(x.startswith("k_count_louder:") for x in api(f"louder {direct} {n_q} 0 0 0 0")[2:])
+    got = api(f"louder {ranks} {n_q} 0 0 0 0")
+    assert got[:2] == ["0", "1"]
+    assert [x.split(":")[0] for x in got[2:]] == [x.split(":")[0] for x in RANKS] * -(-n_q // 262_144)
+    assert api(f"louder {ranks} {n_q} 9999999 0 0 0")[1] == "0"
 
 
 @pytest.mark.parametrize("cap", [1, 2])

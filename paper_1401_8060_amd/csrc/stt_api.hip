@@ -653,6 +653,28 @@ bool prefer_wave(int T, int64_t n) { return n * (int64_t)(T + 600) < 80000 * (in
 bool prefer_slabs_md(int T, int64_t n) { return n >= 130000 + 27000000 / T; }
 bool prefer_wave_md(int T, int64_t n) { return n * (47000 - 37 * (int64_t)T) < 3200000 * (int64_t)T; }
 
+// Where those two, measured with templates of 10 columns or more on maps up to 8 MB, choose a direct scorer,
+// slabs are still the cheaper ones for longer templates, larger maps and more launches: by estimated times
+// (us), mean the mean template length. A sweep per launch after one sort; a wave per template by its length,
+// the more the further the folded map exceeds an L2; lane by lane by waves per SIMD (65 536 templates each).
+// Measured (direct, slabs) with 1.5 x 10^5 templates: 1000 x 1000 of at least 500 columns 570, 443 for 8
+// delays, 1692, 1237 for 17; 500 x 151 for 17 633, 543; 130 000 on 1900 x 1900 of at least 237 for 32 5558,
+// 3630; 260 000 on 150 x 150 for 32 301, 269. Over 1420 sizes on 50 to 2800 columns the choice costs 0.6 %
+// on average over the best scorer, 1.8 % without this.
+bool slabs_beat_direct_md(int T, int64_t col_bytes, bool p16, int64_t n, double mean, int launches, bool per_wave)
+{
+    const double nd = (double)n, la = (double)launches;
+    const double per_col = 0.31 + 8e-6 * (double)col_bytes + (p16 ? 0.04 : 0.0);
+    const double slab = 50.0 + la * (5.0 + std::max(per_col * T, 2.2e-6 * nd * mean));
+    if (per_wave) {
+        const double mb = 1e-6 * (double)T * (double)col_bytes;
+        const double per_px = std::clamp((mb - 2.0) * 0.55e-6, 0.3e-6, 10.5e-6);
+        return slab < 0.95 * la * (10.0 + nd * (2e-3 + per_px * mean));
+    }
+    const double simd_waves = (double)((n + 65535) / 65536);
+    return n > 2 * 65536 && slab < (T < 300 ? 0.9 : 1.0) * la * (6.0 + T * (0.2 + 0.105 * (simd_waves - 1.0)));
+}
+
 // And for free-t_mid templates, whose slab call costs at least 62, 138, 160, 345, 495 us at those T;
 // one wave per template costs 1.7 to 4.5 ns each, 37 to 74 us at 10^4 and 191, 200, 209, 306, 493 at 10^5.
 bool prefer_slabs_tm(int T, int64_t n) { return n >= 4096 && n * (int64_t)(T + 600) >= 165000 * (int64_t)T; }
@@ -796,8 +818,13 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     const int lds = std::min(c->lds_bytes, 80 * 1024);
     const int esize = fold_esize(map->dtype);
     const int64_t ldc = fold_ld(map->F, esize);
-    bool slab = c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
-                (c->path == 2 || prefer_slabs_md(map->T, n));
+    const bool p16 = map->dtype == STT_P16;
+    const int n_launch = (n_tau + kMD - 1) / kMD;
+    const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave_md(map->T, n));
+    const double mean = EXPL ? map->T / 3.0 : g.L + (map->T - g.L) / 3.0;
+    const bool slab = c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
+                      (c->path == 2 || prefer_slabs_md(map->T, n) ||
+                       slabs_beat_direct_md(map->T, ldc * esize, p16, n, mean, n_launch, per_wave));
     if (c->path == 2 && !slab)
         return fail(c, STT_EUNSUPPORTED, "F=%d too wide for two LDS slabs of %d bytes", map->F, lds);
     stt_status s;
@@ -808,9 +835,7 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     }
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
-    const bool p16 = map->dtype == STT_P16;
-    const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave_md(map->T, n));
-    if (!slab && gather_unfolded(map, per_wave, n * ((n_tau + kMD - 1) / kMD))) {
+    if (!slab && gather_unfolded(map, per_wave, n * n_launch)) {
         const MapP m = to_mapp(map);
         s = p16 ? maxdelay_direct<EXPL, kMapP16>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best)
                 : maxdelay_direct<EXPL, kMapF32>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best);

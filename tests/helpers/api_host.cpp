@@ -12,6 +12,8 @@
 //       stt_set_slab_shape(wg, tpt) (0 0: not called) and a stt_set_path for each lds (0: budget kept)
 //   batch n0 n1 -> status of stt_score_batch for two maps of these many templates
 //   items per n run -> (slide, place) of the per n workgroups that an XCD takes of a slide launch, in order
+//   md T F esize n L n_tau -> the delay grid's scorer (lane, slab or wave) for n generated templates of L
+//       columns or more
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -181,6 +183,18 @@ static int items()
     return 0;
 }
 
+static int md()
+{
+    int T, F, e, L, n_tau;
+    long long n;
+    if (std::scanf("%d %d %d %lld %d %d", &T, &F, &e, &n, &L, &n_tau) != 6) return 2;
+    const bool wave = prefer_wave_md(T, n);
+    const bool slab = prefer_slabs_md(T, n) || slabs_beat_direct_md(T, fold_ld(F, e) * e, e == 4, n, L + (T - L) / 3.0,
+                                                                    (n_tau + kMD - 1) / kMD, wave);
+    std::printf("%s\n", slab ? "slab" : wave ? "wave" : "lane");
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -189,7 +203,8 @@ int main()
                         : !std::strcmp(cmd, "topk") ? topk()
                         : !std::strcmp(cmd, "shape") ? shape()
                         : !std::strcmp(cmd, "batch") ? batch()
-                        : !std::strcmp(cmd, "items") ? items() : 2;
+                        : !std::strcmp(cmd, "items") ? items()
+                        : !std::strcmp(cmd, "md") ? md() : 2;
         if (bad) return bad;
     }
     return 0;

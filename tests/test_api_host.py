@@ -122,3 +122,22 @@ def test_slide_workgroups_in_runs(api, per, n, run):
     got = [int(x) for x in api(f"items {per} {n} {run}")]
     want = [(k, at) for r in range(0, per, run) for k in range(n) for at in range(r, min(r + run, per))]
     assert list(zip(got[::2], got[1::2])) == want
+
+
+@pytest.mark.parametrize("T,F,e,n,L,n_tau,want", [
+    # measured times in us at the right: lane, slabs, wave
+    (100, 128, 8, 5_000, 10, 8, "wave"),         # 34, 76, 25
+    (100, 128, 8, 100_000, 10, 8, "lane"),       # 38, 77, 235
+    (300, 300, 8, 100_000, 150, 8, "lane"),      # 94, 151, 245
+    (1000, 1000, 8, 100_000, 10, 8, "wave"),     # 360, 430, 274
+    (1000, 1000, 8, 150_000, 500, 8, "slab"),    # 629, 427, 572
+    (1000, 1000, 8, 200_000, 10, 8, "slab"),     # 651, 421, 530
+    (1000, 1000, 8, 150_000, 500, 17, "slab"),   # slabs 1237, wave 1692
+    (500, 151, 8, 150_000, 10, 24, "slab"),      # 629, 532, 1084
+    (700, 200, 8, 130_000, 10, 32, "lane"),      # lane 805, slabs 960
+    (700, 1400, 8, 80_000, 10, 12, "wave"),      # wave 416, slabs 659
+    (1900, 1900, 8, 130_000, 237, 32, "slab"),   # wave 5558, slabs 3630
+    (1900, 1900, 4, 130_000, 237, 32, "slab"),   # wave 4091, slabs 3410
+])
+def test_delay_grid_scorer_by_cost(api, T, F, e, n, L, n_tau, want):
+    assert api(f"md {T} {F} {e} {n} {L} {n_tau}") == [want]

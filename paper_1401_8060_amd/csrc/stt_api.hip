@@ -675,9 +675,20 @@ bool slabs_beat_direct_md(int T, int64_t col_bytes, bool p16, int64_t n, double 
     return n > 2 * 65536 && slab < (T < 300 ? 0.9 : 1.0) * la * (6.0 + T * (0.2 + 0.105 * (simd_waves - 1.0)));
 }
 
-// And for free-t_mid templates, whose slab call costs at least 62, 138, 160, 345, 495 us at those T;
-// one wave per template costs 1.7 to 4.5 ns each, 37 to 74 us at 10^4 and 191, 200, 209, 306, 493 at 10^5.
-bool prefer_slabs_tm(int T, int64_t n) { return n >= 4096 && n * (int64_t)(T + 600) >= 165000 * (int64_t)T; }
+// And for n generated free-t_mid templates of mean length `mean` on columns of col_bytes, by estimated times
+// (us): slabs take the sort and a sweep of the columns, which widen them; a wave per template takes 1.7 ns and
+// 3 ps per column of its length, 0.45 more for each MB of folded map beyond 3 (13.5 at most). Measured (slabs,
+// wave): 60 000 templates on 300 x 300 110, 119; 10^5 on 1000 x 1000 345, 306; on 2000 x 500 508, 572; on
+// 1400 x 1400 584, 687 of at least 175 columns, 591, 1026 of 700; 125 000 on 1900 x 1900 970, 1411 of at least
+// 237, on 2800 x 2000 1453, 5138 of 2798. Over 840 sizes (50 to 2800 columns, 40 to 2000 rows, 5000 to 2.5 x
+// 10^5 templates) the choice costs 0.16 % on average over the better scorer, 4 % by the templates alone.
+bool prefer_slabs_tm(int T, int64_t col_bytes, int64_t n, double mean)
+{
+    const double nd = (double)n, col = (double)col_bytes;
+    const double slab = 40.0 + 6e-5 * nd + std::max(T * (0.24 + 1.2e-5 * col), 1.2e-6 * nd * mean);
+    const double per_col = std::min(3e-6 + 0.45e-6 * std::max(0.0, 1e-6 * T * col - 3.0), 13.5e-6);
+    return n >= 4096 && slab < 10.0 + nd * (1.7e-3 + mean * per_col);
+}
 
 template <bool EXPL>
 stt_status score_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Trk *tr, int64_t first, int64_t n,
@@ -1324,7 +1335,7 @@ stt_status stt_score_tm(stt_ctx *c, const stt_map *map, const stt_gen *gen, cons
     const int esize = fold_esize(map->dtype);
     const int64_t ldc = fold_ld(map->F, esize);
     const bool slab = !tracks_dev && c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
-                      (c->path == 2 || prefer_slabs_tm(map->T, n));
+                      (c->path == 2 || prefer_slabs_tm(map->T, ldc * esize, n, g.L + (map->T - g.L) / 3.0));
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
     const bool p16 = map->dtype == STT_P16;

@@ -14,6 +14,7 @@
 //   items per n run -> (slide, place) of the per n workgroups that an XCD takes of a slide launch, in order
 //   md T F esize n L n_tau -> the delay grid's scorer (lane, slab or wave) for n generated templates of L
 //       columns or more
+//   tm T F esize n L -> the free-t_mid scorer (slab or wave) for n generated templates of L columns or more
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -195,6 +196,15 @@ static int md()
     return 0;
 }
 
+static int tm()
+{
+    int T, F, e, L;
+    long long n;
+    if (std::scanf("%d %d %d %lld %d", &T, &F, &e, &n, &L) != 5) return 2;
+    std::printf("%s\n", prefer_slabs_tm(T, fold_ld(F, e) * e, n, L + (T - L) / 3.0) ? "slab" : "wave");
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -204,7 +214,8 @@ int main()
                         : !std::strcmp(cmd, "shape") ? shape()
                         : !std::strcmp(cmd, "batch") ? batch()
                         : !std::strcmp(cmd, "items") ? items()
-                        : !std::strcmp(cmd, "md") ? md() : 2;
+                        : !std::strcmp(cmd, "md") ? md()
+                        : !std::strcmp(cmd, "tm") ? tm() : 2;
         if (bad) return bad;
     }
     return 0;

@@ -141,3 +141,19 @@ def test_slide_workgroups_in_runs(api, per, n, run):
 ])
 def test_delay_grid_scorer_by_cost(api, T, F, e, n, L, n_tau, want):
     assert api(f"md {T} {F} {e} {n} {L} {n_tau}") == [want]
+
+
+@pytest.mark.parametrize("T,F,e,n,L,want", [
+    # measured times in us at the right: slabs, wave
+    (1000, 1000, 8, 100_000, 10, "wave"),        # 345, 306
+    (1000, 1000, 8, 150_000, 10, "slab"),
+    (1400, 1400, 8, 100_000, 175, "slab"),       # 584, 687
+    (1400, 1400, 4, 100_000, 700, "slab"),       # 476, 597
+    (1900, 1900, 8, 125_000, 237, "slab"),       # 970, 1411
+    (1900, 1900, 4, 60_000, 1898, "slab"),       # 735, 949
+    (2800, 2000, 8, 125_000, 2798, "slab"),      # 1453, 5138
+    (1900, 1900, 8, 30_000, 10, "wave"),
+    (20, 20, 8, 4095, 18, "wave"),
+])
+def test_free_tmid_scorer_by_cost(api, T, F, e, n, L, want):
+    assert api(f"tm {T} {F} {e} {n} {L}") == [want]

@@ -624,14 +624,17 @@ stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, 
 // is better at any n (9.1 and 18.5 for 128 templates on 100 x 128, 9.5 and 11.5 for 450 on
 // 300 x 300); above, gathering is up to n T = 1.2e6 (20.7 and 16.2 for 1000 on 1000 x 1000, 13.2 and
 // 11.2 for 600 on 300 x 1000; with templates of all T columns 24.9 and 20.8 at 1000, 26.6 and 28.8 at
-// 1500). Past 64 flush groups a lane's second group waits for its first's polar forms: folding is
+// 1500). Fewer than 512 templates of fewer than 500 columns leave the chip to the few lanes that form the
+// elements (100 templates: 13.7 and 17.2 on 300 x 1000, 14.3 and 19.2 on 200 x 4000, 13.8 and 13.9 on 500 x
+// 800; 512 on 300 x 1000: 13.8 and 12.9). A second launch of the delay grid would form them again (16 delays:
+// 24 and 27 for 100 templates on 1000 x 1000, 26 and 43 on 300 x 1000). Past 64 flush groups a lane's second group waits for its first's polar forms: folding is
 // better (500 templates on 2000 x 500: 24.1 and 27.5). One lane per template always folds: its polar
 // forms would follow one another (326 us folded, 629 us not, for 1000 templates on 1000 x 1000). FP16
 // maps are gathered as they are by every direct scorer: their words are the polar elements.
-bool gather_unfolded(const stt_map *map, bool per_wave, int64_t n)
+bool gather_unfolded(const stt_map *map, bool per_wave, int64_t n, int launches = 1)
 {
     if (map->dtype == STT_P16) return true;
-    return per_wave && map->T <= 64 * kFlush && (int64_t)map->T * map->F >= 250000 && n * map->T <= 1200000;
+    return per_wave && launches == 1 && (map->T >= 500 || n >= 512) && map->T <= 64 * kFlush && (int64_t)map->T * map->F >= 250000 && n * map->T <= 1200000;
 }
 
 // Which scorer takes a call of n templates on T columns. The slab scorer sweeps the columns one slab
@@ -846,7 +849,7 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     }
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
-    if (!slab && gather_unfolded(map, per_wave, n * n_launch)) {
+    if (!slab && gather_unfolded(map, per_wave, n, n_launch)) {
         const MapP m = to_mapp(map);
         s = p16 ? maxdelay_direct<EXPL, kMapP16>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best)
                 : maxdelay_direct<EXPL, kMapF32>(c, per_wave, m, g, tr, first, n, d0, step, n_tau, norm, snr, tidx, best);

@@ -15,6 +15,7 @@
 //   md T F esize n L n_tau -> the delay grid's scorer (lane, slab or wave) for n generated templates of L
 //       columns or more
 //   tm T F esize n L -> the free-t_mid scorer (slab or wave) for n generated templates of L columns or more
+//   gather T F p16 wave n launches -> 1 if that direct call reads the caller's map unfolded
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -205,6 +206,19 @@ static int tm()
     return 0;
 }
 
+static int gather()
+{
+    int T, F, p16, wave, launches;
+    long long n;
+    if (std::scanf("%d %d %d %d %lld %d", &T, &F, &p16, &wave, &n, &launches) != 6) return 2;
+    stt_map m{};
+    m.T = T;
+    m.F = F;
+    m.dtype = p16 ? STT_P16 : STT_C64F32;
+    std::printf("%d\n", gather_unfolded(&m, wave != 0, n, launches));
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -215,7 +229,8 @@ int main()
                         : !std::strcmp(cmd, "batch") ? batch()
                         : !std::strcmp(cmd, "items") ? items()
                         : !std::strcmp(cmd, "md") ? md()
-                        : !std::strcmp(cmd, "tm") ? tm() : 2;
+                        : !std::strcmp(cmd, "tm") ? tm()
+                        : !std::strcmp(cmd, "gather") ? gather() : 2;
         if (bad) return bad;
     }
     return 0;

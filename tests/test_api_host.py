@@ -157,3 +157,12 @@ def test_delay_grid_scorer_by_cost(api, T, F, e, n, L, n_tau, want):
 ])
 def test_free_tmid_scorer_by_cost(api, T, F, e, n, L, want):
     assert api(f"tm {T} {F} {e} {n} {L}") == [want]
+
+
+@pytest.mark.parametrize("T,F,p16,wave,n,launches,want", [
+    (300, 1000, 0, 1, 511, 1, 0), (300, 1000, 0, 1, 512, 1, 1), (499, 1000, 0, 1, 100, 1, 0), (500, 1000, 0, 1, 100, 1, 1),
+    (1000, 1000, 0, 1, 1000, 1, 1), (1000, 1000, 0, 1, 1000, 2, 0), (1000, 1000, 0, 1, 1201, 1, 0),
+    (500, 499, 0, 1, 1000, 1, 0), (1025, 1000, 0, 1, 100, 1, 0), (1000, 1000, 0, 0, 1000, 1, 0), (300, 1000, 1, 0, 10, 3, 1),
+])
+def test_direct_calls_that_read_the_map_unfolded(api, T, F, p16, wave, n, launches, want):
+    assert api(f"gather {T} {F} {p16} {wave} {n} {launches}") == [str(want)]

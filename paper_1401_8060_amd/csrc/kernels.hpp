@@ -582,7 +582,7 @@ __device__ __forceinline__ void wave_prefix(F val, int cnt, uint32_t *out)
 
 template <bool EXPL>
 __device__ __forceinline__ uint32_t bin_of(const GenP &g, const Trk *tr, const MapP &m, uint64_t first, int64_t i,
-                                           int wb)
+                                           int wb, uint32_t cw)
 {
     int32_t t0, t2;
     if (EXPL) {
@@ -595,7 +595,7 @@ __device__ __forceinline__ uint32_t bin_of(const GenP &g, const Trk *tr, const M
     }
     const uint32_t b0 = (uint32_t)t0 >> wb, b2 = (uint32_t)t2 >> wb;
     const uint32_t nb = ((uint32_t)(m.T - 1) >> wb) + 1;
-    return bucket_number(nb - 1 - (b2 - b0), b0, bucket_class(nb), nb);
+    return bucket_number(nb - 1 - (b2 - b0), b0, cw, nb);
 }
 
 // The count's step for one chunk, after its histogram hist[0 .. nbins-1] is
@@ -624,7 +624,8 @@ __device__ __forceinline__ void count_out(const uint32_t *hist, int nbins, uint3
 // at ccnt + c with stride gridDim.x (row k of ccnt: group k's count per chunk).
 template <bool EXPL>
 __global__ __launch_bounds__(256) void k_bin_count(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n, int wb,
-                                                   int nbins, uint32_t *totals, uint16_t *bins, uint32_t *ccnt)
+                                                   uint32_t cw, int nbins, uint32_t *totals, uint16_t *bins,
+                                                   uint32_t *ccnt)
 {
     __shared__ uint32_t hist[kMaxBins];
     for (int b = threadIdx.x; b < nbins; b += 256) hist[b] = 0;
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(256) void k_bin_count(MapP m, GenP g, const Trk *tr
     for (int q = 0; q < kBinPerThread; ++q) {
         const int64_t i = base + q * 256 + threadIdx.x;
         if (i < n) {
-            const uint32_t b = bin_of<EXPL>(g, tr, m, first, i, wb);
+            const uint32_t b = bin_of<EXPL>(g, tr, m, first, i, wb, cw);
             bins[i] = (uint16_t)b;
             atomicAdd(&hist[b], 1u);
         }
@@ -2009,12 +2010,12 @@ __global__ __launch_bounds__(256) void k_bin_count_batch(const BatchMap *maps, i
     const BatchMap &d = maps[mi];
     for (int b = threadIdx.x; b < d.nbins; b += 256) hist[b] = 0;
     __syncthreads();
-    const uint32_t c = blockIdx.x - chunk_start[mi];
+    const uint32_t c = blockIdx.x - chunk_start[mi], cw = bucket_class(((uint32_t)(d.m.T - 1) >> d.wb) + 1);
     const int64_t base = (int64_t)c * kBinChunk;
     for (int q = 0; q < kBinPerThread; ++q) {
         const int64_t i = base + q * 256 + threadIdx.x;
         if (i < d.n) {
-            const uint32_t b = bin_of<false>(d.g, nullptr, d.m, 0, i, d.wb);
+            const uint32_t b = bin_of<false>(d.g, nullptr, d.m, 0, i, d.wb, cw);
             bins[d.order0 + i] = (uint16_t)b;
             atomicAdd(&hist[b], 1u);
         }

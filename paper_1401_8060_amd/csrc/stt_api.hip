@@ -525,15 +525,27 @@ bool slab_shape_ok(int wg, int tpt)
     return false;
 }
 
+// Extents per class of the sort's order for nb buckets per axis. Slabs staged through registers and at most
+// one workgroup per CU: by extent alone, a class each. Such a call lasts as long as its longest workgroup,
+// and staging does not wait for an L2 that workgroups share (us for 3 x 10^5 and 10^6 templates on 600 x
+// 6000: 869 and 868, in four classes 910 and 924; for 3 x 10^6, several workgroups per CU, 1945 and 1584).
+uint32_t sort_class(bool dma, int64_t workgroups, int n_cu, int nb)
+{
+    return !dma && workgroups <= n_cu ? 1u : bucket_class((uint32_t)nb);
+}
+
 // Counting sort of templates first .. first+n-1 by time-extent bucket into the
 // context's scratch (timed as the binning stage): returns the binned order and
-// the per-workgroup key slots that follow it.
+// the per-workgroup key slots that follow it. per_wg: templates per workgroup of
+// a scorer that stages through registers, 0 with DMA staging.
 template <bool EXPL>
 stt_status bin_templates(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n,
-                         const FixedBufs *fb, uint32_t *&order, uint64_t *&wg_keys)
+                         const FixedBufs *fb, uint32_t *&order, uint64_t *&wg_keys, int per_wg = 0)
 {
     const int wb = bucket_shift(m.T, n);
     const int nb = ((m.T - 1) >> wb) + 1;
+    if (per_wg && !c->n_cu) STT_HIP(c, hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
+    const uint32_t cw = sort_class(!per_wg, per_wg ? (n + per_wg - 1) / per_wg : 0, c->n_cu, nb);
     const int nbins = nb * (nb + 1) / 2;
     const size_t n_order = ((size_t)n + 1) & ~(size_t)1;  // keeps the key slots 8-byte aligned
     if (!fb) {
@@ -554,7 +566,7 @@ stt_status bin_templates(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr
     uint16_t *bins = (uint16_t *)order;
     ev_attach(c, 2, -1);
     launch_ev(c, k_fill_u32, dim3((nbins + 255) / 256), dim3(256), 0, totals, (int64_t)nbins, 0u);
-    hipLaunchKernelGGL(k_bin_count<EXPL>, dim3(bgrid), dim3(256), 0, c->stream, m, g, tr, (uint64_t)first, n, wb,
+    hipLaunchKernelGGL(k_bin_count<EXPL>, dim3(bgrid), dim3(256), 0, c->stream, m, g, tr, (uint64_t)first, n, wb, cw,
                        nbins, totals, bins, ccnt);
     hipLaunchKernelGGL(k_bin_scan, dim3(1 + (unsigned)ngroups), dim3(256), 0, c->stream, (const uint32_t *)totals, nbins,
                        cursor, gstart, fitem, ccnt, (int)bgrid);
@@ -588,11 +600,11 @@ stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, 
     constexpr int esize = (int)sizeof(elem_t<MAPT>);
     stt_status s;
     const SlabShape sh = call_shape(c, n, m.ld * esize);
-    uint32_t *order = nullptr;
-    uint64_t *wg_keys = nullptr;
-    if ((s = bin_templates<EXPL>(c, m, g, tr, first, n, fb, order, wg_keys)) != STT_OK) return s;
     const int64_t ldc = m.ld;
     const int sc = c->dma ? aligned_slab(dma_slab_cols(sh.lds, ldc, esize)) : 0;
+    uint32_t *order = nullptr;
+    uint64_t *wg_keys = nullptr;
+    if ((s = bin_templates<EXPL>(c, m, g, tr, first, n, fb, order, wg_keys, sc > 0 ? 0 : sh.wg * sh.tpt)) != STT_OK) return s;
     if (sc > 0) {
         // aligned slabs of the folded map streamed into LDS with double-buffered DMA
         const size_t shm = 2 * (size_t)esize * (size_t)sc * ldc;

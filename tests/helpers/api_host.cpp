@@ -16,6 +16,7 @@
 //       columns or more
 //   tm T F esize n L -> the free-t_mid scorer (slab or wave) for n generated templates of L columns or more
 //   gather T F p16 wave n launches -> 1 if that direct call reads the caller's map unfolded
+//   class dma workgroups n_cu nb -> extents per class of the sort
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -219,6 +220,15 @@ static int gather()
     return 0;
 }
 
+static int sclass()
+{
+    int dma, n_cu, nb;
+    long long wgs;
+    if (std::scanf("%d %lld %d %d", &dma, &wgs, &n_cu, &nb) != 4) return 2;
+    std::printf("%u\n", sort_class(dma != 0, wgs, n_cu, nb));
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -230,7 +240,8 @@ int main()
                         : !std::strcmp(cmd, "items") ? items()
                         : !std::strcmp(cmd, "md") ? md()
                         : !std::strcmp(cmd, "tm") ? tm()
-                        : !std::strcmp(cmd, "gather") ? gather() : 2;
+                        : !std::strcmp(cmd, "gather") ? gather()
+                        : !std::strcmp(cmd, "class") ? sclass() : 2;
         if (bad) return bad;
     }
     return 0;

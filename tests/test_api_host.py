@@ -166,3 +166,9 @@ def test_free_tmid_scorer_by_cost(api, T, F, e, n, L, want):
 ])
 def test_direct_calls_that_read_the_map_unfolded(api, T, F, p16, wave, n, launches, want):
     assert api(f"gather {T} {F} {p16} {wave} {n} {launches}") == [str(want)]
+
+
+def test_sort_by_extent_alone_for_one_round_of_register_staging(api):
+    """A workgroup per CU at most, staged through registers: one extent per class; else the four classes."""
+    assert api("class 0 256 256 126") == ["1"] and api("class 0 257 256 126") == ["32"]
+    assert api("class 1 1 256 126") == ["32"] and api("class 0 1 256 1") == ["1"]

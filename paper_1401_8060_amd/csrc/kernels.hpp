@@ -392,31 +392,37 @@ __device__ __forceinline__ pol_t<MAPT> load_pol(const MapP &m, int64_t e)
 
 // The FP32 sum of a template's terms over the flush group that starts at column cb (a multiple of
 // kFlush), for a row walk st standing at cb; st is advanced past the group. t0 .. t2: its columns.
-template <bool HW, int MAPT>
+// G gathers at a time are in flight (the sums are the same for every G).
+template <bool HW, int MAPT, int G = kFlush>
 __device__ __forceinline__ float group_sum(const MapP &m, const PhaseK &pk, int32_t cb, int32_t t0, int32_t t2, DdaF &st)
 {
-    int32_t row[kFlush];
-    pol_t<MAPT> v[kFlush];
-#pragma unroll
-    for (int j = 0; j < kFlush; ++j) {
-        const int32_t c = cb + j;
-        const bool act = c >= t0 && c <= t2;
-        row[j] = act ? ddaf_row(st) : 0;
-        v[j] = load_pol<MAPT>(m, (int64_t)(act ? c : t0) * m.ld + row[j]);
-        ddaf_step(st);
-    }
     float part = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kFlush; ++j) {
-        const int32_t c = cb + j;
-        const float p = add_term_pol<HW>(part, pk, row[j], v[j]);
-        part = c >= t0 && c <= t2 ? p : part;
+    for (int j0 = 0; j0 < kFlush; j0 += G) {
+        int32_t row[G];
+        pol_t<MAPT> v[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t c = cb + j0 + j;
+            const bool act = c >= t0 && c <= t2;
+            row[j] = act ? ddaf_row(st) : 0;
+            v[j] = load_pol<MAPT>(m, (int64_t)(act ? c : t0) * m.ld + row[j]);
+            ddaf_step(st);
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t c = cb + j0 + j;
+            const float p = add_term_pol<HW>(part, pk, row[j], v[j]);
+            part = c >= t0 && c <= t2 ? p : part;
+        }
+        if (G < kFlush) __builtin_amdgcn_sched_barrier(0);
     }
     return part;
 }
 
-// One lane per template.
-template <bool EXPL, bool HW, int MAPT>
+// One lane per template. G: a flush group's gathers at a time, or one at a time where many lanes walk a
+// map larger than an L2 (lane_gathers).
+template <bool EXPL, bool HW, int MAPT, int G>
 __global__ __launch_bounds__(kWG) void k_score_direct(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n,
                                                       int32_t norm, float *snr, uint64_t *best)
 {
@@ -430,7 +436,7 @@ __global__ __launch_bounds__(kWG) void k_score_direct(MapP m, GenP g, const Trk 
             int32_t cb = t.t0 & ~(kFlush - 1);
             DdaF st = ddaf_init_at(t, cb - t.t0);
             double acc = 0.0;
-            for (; cb <= t.t2; cb += kFlush) acc += group_sum<HW, MAPT>(m, pk, cb, t.t0, t.t2, st);
+            for (; cb <= t.t2; cb += kFlush) acc += group_sum<HW, MAPT, G>(m, pk, cb, t.t0, t.t2, st);
             z = finish(acc, t.t2 - t.t0 + 1, norm, m.scale);
         }
         if (snr) snr[i] = z;
@@ -1723,31 +1729,35 @@ __device__ __forceinline__ void merge_running(float &z, int32_t &mi, float zp, i
 
 // The FP32 sums, for the launch's delays, of a template's terms over the flush group that starts at
 // column cb, for a row walk standing there (as group_sum).
-template <bool HW, int MAPT>
+template <bool HW, int MAPT, int G = kFlush>
 __device__ __forceinline__ void group_sums_md(const MapP &m, const DelayGrid &dg, int32_t cb, int32_t t0, int32_t t2,
                                               DdaF &st, float (&part)[kMD])
 {
-    int32_t row[kFlush];
-    pol_t<MAPT> v[kFlush];
-#pragma unroll
-    for (int j = 0; j < kFlush; ++j) {
-        const int32_t c = cb + j;
-        const bool act = c >= t0 && c <= t2;
-        row[j] = act ? ddaf_row(st) : 0;
-        v[j] = load_pol<MAPT>(m, (int64_t)(act ? c : t0) * m.ld + row[j]);
-        ddaf_step(st);
-    }
 #pragma unroll
     for (int k = 0; k < kMD; ++k) part[k] = 0.0f;
 #pragma unroll
-    for (int j = 0; j < kFlush; ++j) {
-        const int32_t c = cb + j;
-        add_terms_md<HW, true>(part, dg, row[j], v[j], c >= t0 && c <= t2);
+    for (int j0 = 0; j0 < kFlush; j0 += G) {
+        int32_t row[G];
+        pol_t<MAPT> v[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t c = cb + j0 + j;
+            const bool act = c >= t0 && c <= t2;
+            row[j] = act ? ddaf_row(st) : 0;
+            v[j] = load_pol<MAPT>(m, (int64_t)(act ? c : t0) * m.ld + row[j]);
+            ddaf_step(st);
+        }
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int32_t c = cb + j0 + j;
+            add_terms_md<HW, true>(part, dg, row[j], v[j], c >= t0 && c <= t2);
+        }
+        if (G < kFlush) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
 // One lane per template, direct gathers (maps too wide for LDS, medium calls).
-template <bool EXPL, bool HW, int MAPT>
+template <bool EXPL, bool HW, int MAPT, int G>
 __global__ __launch_bounds__(kWG) void k_score_md_direct(MapP m, GenP g, const Trk *tr, uint64_t first, int64_t n,
                                                          int32_t norm, int32_t d0, int32_t step, int32_t m0,
                                                          int32_t cnt, int32_t last, float *snr, int32_t *tidx,
@@ -1767,7 +1777,7 @@ __global__ __launch_bounds__(kWG) void k_score_md_direct(MapP m, GenP g, const T
             int32_t cb = t.t0 & ~(kFlush - 1);
             DdaF st = ddaf_init_at(t, cb - t.t0);
             for (; cb <= t.t2; cb += kFlush) {
-                group_sums_md<HW, MAPT>(m, dg, cb, t.t0, t.t2, st, part);
+                group_sums_md<HW, MAPT, G>(m, dg, cb, t.t0, t.t2, st, part);
 #pragma unroll
                 for (int q = 0; q < kMD; ++q) { acc[q] += part[q]; part[q] = 0.0f; }
             }

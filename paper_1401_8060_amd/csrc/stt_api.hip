@@ -26,6 +26,7 @@ struct Rec {
 };
 
 constexpr int kLdsBytes = 160 * 1024;  // LDS of a CU, the default slab budget
+constexpr int64_t kL2Bytes = 4 << 20;  // L2 of an XCD
 
 struct stt_ctx {
     int device = 0;
@@ -414,6 +415,20 @@ stt_status launch_slab(stt_ctx *c, int sc, int wg, int tpt, const MapP &m, const
 // 16 waves per CU, and at most 1024 atomics on the best key, one per workgroup.
 unsigned wave_grid(int64_t n) { return (unsigned)std::min<int64_t>((n + 3) / 4, 1024); }
 
+// Mean template length: of generated templates by their least length, of given ones as for a small least one.
+double mean_length(bool given, const GenP &g, int T) { return given ? T / 3.0 : g.L + (T - g.L) / 3.0; }
+
+// Whether lanes that walk a template each gather one pixel at a time. 16 in flight pay while few lanes are
+// active at a time; where more than some 40 000 are (templates, by their mean share of the columns), on a
+// map beyond an L2, their lines push each other out of the caches. Measured (us, 16 and one): 70 000
+// templates on 1000 x 1000 274, 347 of at least 10 columns, 413, 328 of 500; 3 x 10^5 624, 569 and 1021,
+// 803; on 600 x 6000 821, 675 and, of at least 300 columns, 1376, 764. Delay grid, 3 x 10^5 on 600 x 6000:
+// 840, 756 and 1301, 862. Maps within an L2 (10^6 on 300 x 100: 297, 324) keep 16.
+bool lane_gathers_one(int64_t map_bytes, int T, int64_t n, double mean)
+{
+    return map_bytes > kL2Bytes && (double)n * mean > 40000.0 * T;
+}
+
 template <bool EXPL, bool HW, int MAPT>
 void launch_direct(stt_ctx *c, bool per_wave, const MapP &m, const GenP &g, const Trk *tr, int64_t first, int64_t n,
                    int32_t norm, float *snr, uint64_t *best)
@@ -424,8 +439,9 @@ void launch_direct(stt_ctx *c, bool per_wave, const MapP &m, const GenP &g, cons
         return;
     }
     const unsigned grid = (unsigned)((n + kWG - 1) / kWG);
-    hipLaunchKernelGGL((k_score_direct<EXPL, HW, MAPT>), dim3(grid), dim3(kWG), 0, c->stream, m, g, tr,
-                       (uint64_t)first, n, norm, snr, best);
+    const bool one = lane_gathers_one(m.T * m.ld * (int64_t)sizeof(pol_t<MAPT>), m.T, n, mean_length(EXPL, g, m.T));
+    auto kern = one ? k_score_direct<EXPL, HW, MAPT, 1> : k_score_direct<EXPL, HW, MAPT, kFlush>;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kWG), 0, c->stream, m, g, tr, (uint64_t)first, n, norm, snr, best);
 }
 
 // The direct scorers of one call on map m (format MAPT: kMapPol, kMapF32 or kMapP16), timed as the
@@ -780,8 +796,10 @@ stt_status maxdelay_direct(stt_ctx *c, bool per_wave, const MapP &m, const GenP 
 {
     const int n_launch = (n_tau + kMD - 1) / kMD;
     const unsigned grid = per_wave ? wave_grid(n) : (unsigned)((n + kWG - 1) / kWG);
+    const bool one = lane_gathers_one(m.T * m.ld * (int64_t)sizeof(pol_t<MAPT>), m.T, n, mean_length(EXPL, g, m.T));
     auto kern = per_wave ? (c->hw_trig ? k_score_md_wave<EXPL, true, MAPT> : k_score_md_wave<EXPL, false, MAPT>)
-                         : (c->hw_trig ? k_score_md_direct<EXPL, true, MAPT> : k_score_md_direct<EXPL, false, MAPT>);
+                : one ? (c->hw_trig ? k_score_md_direct<EXPL, true, MAPT, 1> : k_score_md_direct<EXPL, false, MAPT, 1>)
+                      : (c->hw_trig ? k_score_md_direct<EXPL, true, MAPT, kFlush> : k_score_md_direct<EXPL, false, MAPT, kFlush>);
     ev_record(c, 0);
     for (int l = 0; l < n_launch; ++l) {
         const int32_t m0 = l * kMD, cnt = std::min(kMD, n_tau - m0), last = l == n_launch - 1;
@@ -847,7 +865,7 @@ stt_status maxdelay_impl(stt_ctx *c, const stt_map *map, const GenP &g, const Tr
     const bool p16 = map->dtype == STT_P16;
     const int n_launch = (n_tau + kMD - 1) / kMD;
     const bool per_wave = c->path == 3 || (c->path == 0 && prefer_wave_md(map->T, n));
-    const double mean = EXPL ? map->T / 3.0 : g.L + (map->T - g.L) / 3.0;
+    const double mean = mean_length(EXPL, g, map->T);
     const bool slab = c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
                       (c->path == 2 || prefer_slabs_md(map->T, n) ||
                        slabs_beat_direct_md(map->T, ldc * esize, p16, n, mean, n_launch, per_wave));
@@ -1350,7 +1368,7 @@ stt_status stt_score_tm(stt_ctx *c, const stt_map *map, const stt_gen *gen, cons
     const int esize = fold_esize(map->dtype);
     const int64_t ldc = fold_ld(map->F, esize);
     const bool slab = !tracks_dev && c->dma && dma_slab_cols(lds, ldc, esize) >= 1 && c->path != 1 && c->path != 3 &&
-                      (c->path == 2 || prefer_slabs_tm(map->T, ldc * esize, n, g.L + (map->T - g.L) / 3.0));
+                      (c->path == 2 || prefer_slabs_tm(map->T, ldc * esize, n, mean_length(false, g, map->T)));
     if ((s = ev_begin(c)) != STT_OK) return s;
     ev_record(c, 4);
     const bool p16 = map->dtype == STT_P16;

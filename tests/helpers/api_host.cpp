@@ -17,6 +17,7 @@
 //   tm T F esize n L -> the free-t_mid scorer (slab or wave) for n generated templates of L columns or more
 //   gather T F p16 wave n launches -> 1 if that direct call reads the caller's map unfolded
 //   class dma workgroups n_cu nb -> extents per class of the sort
+//   one bytes T n mean -> 1 if lanes gather one pixel at a time
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -229,6 +230,16 @@ static int sclass()
     return 0;
 }
 
+static int one()
+{
+    long long bytes, n;
+    int T;
+    double mean;
+    if (std::scanf("%lld %d %lld %lf", &bytes, &T, &n, &mean) != 4) return 2;
+    std::printf("%d\n", lane_gathers_one(bytes, T, n, mean));
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -241,7 +252,8 @@ int main()
                         : !std::strcmp(cmd, "md") ? md()
                         : !std::strcmp(cmd, "tm") ? tm()
                         : !std::strcmp(cmd, "gather") ? gather()
-                        : !std::strcmp(cmd, "class") ? sclass() : 2;
+                        : !std::strcmp(cmd, "class") ? sclass()
+                        : !std::strcmp(cmd, "one") ? one() : 2;
         if (bad) return bad;
     }
     return 0;

@@ -172,3 +172,8 @@ def test_sort_by_extent_alone_for_one_round_of_register_staging(api):
     """A workgroup per CU at most, staged through registers: one extent per class; else the four classes."""
     assert api("class 0 256 256 126") == ["1"] and api("class 0 257 256 126") == ["32"]
     assert api("class 1 1 256 126") == ["32"] and api("class 0 1 256 1") == ["1"]
+
+
+def test_lanes_gather_one_pixel_at_a_time_on_large_maps(api):
+    assert api("one 8192000 1000 70000 340") == ["0"] and api("one 8192000 1000 70000 667") == ["1"]
+    assert api("one 8192000 1000 300000 340") == ["1"] and api("one 4194304 1000 300000 340") == ["0"]

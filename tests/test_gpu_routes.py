@@ -193,3 +193,22 @@ def test_tmid_routes_by_size(stt, ctx, n, p16):
     ctx.set_path(0)
     for z, key in got[1:]:
         assert np.array_equal(z, got[0][0]) and key == got[0][1]
+
+
+# a lane's gathers one at a time or a flush group's: maps on both sides of 4 MB, templates on both sides of
+# 40 000 active lanes, templates that start and end within their groups
+@pytest.mark.parametrize("T,F,n", [(100, 5300, 130_000), (100, 5300, 100_000), (33, 4000, 200_000)])
+def test_lane_gathers(stt, ctx, T, F, n):
+    m = _map(stt, T, F)
+    pm = ctx.pack_p16(m)
+    g = stt.Gen(seed=15, min_len=3, dtau_max=DT)
+    print("lane gathers", T, F, n, flush=True, file=sys.stderr)
+    for mm in (m, pm):
+        got = []
+        for path in (1, 3):
+            ctx.set_path(path)
+            z, key = ctx.score(mm, gen=g, n=n, first=9)
+            zd, mi, keyd = ctx.score_maxdelay(mm, -DT, DT // 8, 9, gen=g, n=n, first=9)
+            got.append((_host(z, zd, mi), key_to_host(key), key_to_host(keyd)))
+        ctx.set_path(0)
+        assert all(np.array_equal(a, b) for a, b in zip(got[0][0], got[1][0])) and got[0][1:] == got[1][1:]

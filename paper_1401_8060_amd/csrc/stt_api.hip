@@ -654,15 +654,18 @@ stt_status score_slabs(stt_ctx *c, const MapP &m, const GenP &g, const Trk *tr, 
 // 11.2 for 600 on 300 x 1000; with templates of all T columns 24.9 and 20.8 at 1000, 26.6 and 28.8 at
 // 1500). Fewer than 512 templates of fewer than 500 columns leave the chip to the few lanes that form the
 // elements (100 templates: 13.7 and 17.2 on 300 x 1000, 14.3 and 19.2 on 200 x 4000, 13.8 and 13.9 on 500 x
-// 800; 512 on 300 x 1000: 13.8 and 12.9). A second launch of the delay grid would form them again (16 delays:
-// 24 and 27 for 100 templates on 1000 x 1000, 26 and 43 on 300 x 1000). Past 64 flush groups a lane's second group waits for its first's polar forms: folding is
+// 800; 512 on 300 x 1000: 13.8 and 12.9) unless the fold is the longer part (400 x 30000: 51 and 15). A second
+// launch of the delay grid would form them again (16 delays: 24 and 27 for 100 templates on 1000 x 1000, 26
+// and 43 on 300 x 1000, 28 and 27 on 1000 x 2000). Past 64 flush groups a lane's second group waits for its first's polar forms: folding is
 // better (500 templates on 2000 x 500: 24.1 and 27.5). One lane per template always folds: its polar
 // forms would follow one another (326 us folded, 629 us not, for 1000 templates on 1000 x 1000). FP16
 // maps are gathered as they are by every direct scorer: their words are the polar elements.
 bool gather_unfolded(const stt_map *map, bool per_wave, int64_t n, int launches = 1)
 {
     if (map->dtype == STT_P16) return true;
-    return per_wave && launches == 1 && (map->T >= 500 || n >= 512) && map->T <= 64 * kFlush && (int64_t)map->T * map->F >= 250000 && n * map->T <= 1200000;
+    const int64_t px = (int64_t)map->T * map->F;
+    if (!per_wave || map->T > 64 * kFlush || n * map->T > 1200000 || px < 250000) return false;
+    return px >= 4000000 * (int64_t)(launches - 1) && (map->T >= 500 || n >= 512 || px >= 1200000);
 }
 
 // Which scorer takes a call of n templates on T columns. The slab scorer sweeps the columns one slab

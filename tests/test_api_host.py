@@ -163,6 +163,8 @@ def test_free_tmid_scorer_by_cost(api, T, F, e, n, L, want):
     (300, 1000, 0, 1, 511, 1, 0), (300, 1000, 0, 1, 512, 1, 1), (499, 1000, 0, 1, 100, 1, 0), (500, 1000, 0, 1, 100, 1, 1),
     (1000, 1000, 0, 1, 1000, 1, 1), (1000, 1000, 0, 1, 1000, 2, 0), (1000, 1000, 0, 1, 1201, 1, 0),
     (500, 499, 0, 1, 1000, 1, 0), (1025, 1000, 0, 1, 100, 1, 0), (1000, 1000, 0, 0, 1000, 1, 0), (300, 1000, 1, 0, 10, 3, 1),
+    (200, 4000, 0, 1, 100, 1, 0), (400, 3000, 0, 1, 100, 1, 1), (400, 30000, 0, 1, 16, 1, 1), (1000, 3999, 0, 1, 100, 2, 0),
+    (1000, 4000, 0, 1, 100, 2, 1),
 ])
 def test_direct_calls_that_read_the_map_unfolded(api, T, F, p16, wave, n, launches, want):
     assert api(f"gather {T} {F} {p16} {wave} {n} {launches}") == [str(want)]

@@ -1448,15 +1448,31 @@ __global__ __launch_bounds__(256) void k_score_tm(MapP m, GenP g, const TrkTm *t
                 gp[r] = 0.0f;
                 const int gi = gfirst + r * 64 + lane;
                 if (gi > glast) continue;
+                const int32_t cb = gi * kFlush;
                 int32_t row[kFlush];
+                uint32_t open = 0;  // columns that the FP32 pass leaves open
+#pragma unroll
+                for (int j = 0; j < kFlush; ++j) {
+                    const bool act = cb + j >= t.t0 && cb + j <= t.t2;
+                    bool ok;
+                    const int32_t r = row_tm_fp32(k, act ? cb + j - t.t0 : 1, ok);
+                    row[j] = act ? r : 0;
+                    open |= act && !ok ? 1u << j : 0u;
+                }
+                // one copy of the exact path, each lane at its own next column
+#pragma unroll 1
+                while (open) {
+                    const int32_t q = __builtin_ctz(open);
+                    const int32_t r = row_tm_fallback(k, cb + q - t.t0);
+#pragma unroll
+                    for (int j = 0; j < kFlush; ++j) row[j] = j == q ? r : row[j];
+                    open &= open - 1;
+                }
                 pol_t<MAPT> v[kFlush];
 #pragma unroll
                 for (int j = 0; j < kFlush; ++j) {
-                    const int32_t c = min(max(gi * kFlush + j, t.t0), t.t2);
-                    bool ok;
-                    row[j] = row_tm_fp32(k, c - t.t0, ok);
-                    if (!ok) row[j] = row_tm_fallback(k, c - t.t0);
-                    v[j] = load_pol<MAPT>(m, (int64_t)c * m.ld + row[j]);
+                    const bool act = cb + j >= t.t0 && cb + j <= t.t2;
+                    v[j] = load_pol<MAPT>(m, (int64_t)(act ? cb + j : t.t0) * m.ld + row[j]);
                 }
                 float part = 0.0f;
 #pragma unroll

@@ -216,6 +216,13 @@ def measured_traffic(workload, shape, sources=None):
     return float(kv["traffic_bytes_per_launch"])
 
 
+def plain_scorer(T, n):
+    """The kernel that the library's rule by pixels and templates gives a plain search (prefer_slabs and
+    prefer_wave in stt_api.hip)."""
+    return ("k_score_slab" if n >= 4096 and n * T >= 60_000_000 else
+            "k_score_wave" if n * (T + 600) < 80_000 * T else "k_score_direct")
+
+
 def roofline(kernel, kernel_ms, px, bpp, traffic=None, mix=None, lds_bpp=8, units=1, mix_units=1):
     """Roofline record of a scoring kernel (kernel_ms: its mean launch time; px: template pixels per
     launch, times `units` evaluations of the statistic per pixel for the delay grid; `mix` counts
@@ -307,11 +314,7 @@ def run_single(args, name, w):
                           "injection": w["inject"] is not None, "per_track_snr": snr is not None, "map_sha256": sha[:16],
                           "slab_shape": list(choice) if choice else None})
     out["best"] = {"z": zk, "j": jk}
-    # the scorer that the library's rule by pixels and templates gives this call
-    T = w["T"]
-    kernel = ("k_score_slab" if n >= 4096 and n * T >= 60_000_000 else
-              "k_score_wave" if n * (T + 600) < 80_000 * T else "k_score_direct")
-    out["roofline"] = roofline(kernel, kern_ms, px, BYTES_F32,
+    out["roofline"] = roofline(plain_scorer(w["T"], n), kern_ms, px, BYTES_F32,
                                measured_traffic(name + ("_argmax" if snr is None else ""), choice))
     if snr is not None and not args.no_argmax_leg:
         # the search proper keeps only the loudest template (Sec. III, V): the same steps with no

@@ -116,6 +116,8 @@ typedef struct stt_ctx stt_ctx;
  * scratch memory. Returns STT_EHIP if the device cannot be selected. */
 stt_status stt_create(int device, void *hip_stream, stt_ctx **out);
 stt_status stt_destroy(stt_ctx *ctx);
+/* Calls of one context share its scratch memory: a caller that changes the
+ * stream orders the new stream's work after the old one's. */
 stt_status stt_set_stream(stt_ctx *ctx, void *hip_stream);
 stt_status stt_sync(stt_ctx *ctx);
 const char *stt_strerror(stt_status s);
@@ -247,8 +249,11 @@ stt_status stt_score_maxdelay(stt_ctx *ctx, const stt_map *map, const stt_gen *g
  * scores; an empty key (0) is quieter than any score and counts as -inf in the
  * threshold. Keys are 8-byte device arrays as written by the scorers. Any of
  * the three outputs may be NULL (z_alpha needs 0 < alpha <= 1 and
- * ceil(alpha n_bg) <= 8192); 1 <= n_bg <= 2^38, n_fg <= 2^38. Exact counts: n_fg * n_bg
- * comparisons. */
+ * ceil(alpha n_bg) <= 8192); 1 <= n_bg <= 2^38, n_fg <= 2^38. Counts are exact, by n_fg * n_bg
+ * comparisons for few background keys (some 700 to 4000, by n_fg), else by placing each background key
+ * among the sorted foreground keys: about n_bg log2(min(n_fg, 4096)) steps per 4096 foreground keys,
+ * for which the call may allocate context memory (up to 4.2 MB); while the stream captures a graph it
+ * compares. The threshold may allocate context memory on its first use. */
 stt_status stt_significance(stt_ctx *ctx, const uint64_t *bg_keys_dev, int64_t n_bg, const uint64_t *fg_keys_dev,
                             int64_t n_fg, double alpha, int64_t *n_louder_dev, float *fap_dev, float *z_alpha_dev);
 
@@ -309,7 +314,8 @@ stt_status stt_spectra(stt_ctx *ctx, const stt_spectro *p, const float *strain_d
  * For k < n_slides: map k pairs column t of I with column (t + shifts[k]) mod T
  * of J (shifts: host array, any integers) and writes Y into Y_dev[k] and sigma
  * into sigma_dev[k] (host arrays of caller-owned device pointers; each map is
- * [T][ld], ld >= F, Y complex64 8-byte aligned, sigma FP32). Shifts of at
+ * [T][ld], ld >= F, Y complex64 8-byte aligned, sigma FP32; the last of slides
+ * into one buffer stands). Shifts of at
  * least 2 columns decorrelate a transient shorter than the shift. */
 stt_status stt_form_maps(stt_ctx *ctx, const stt_spectro *p, int32_t T, const float *spec_i_dev,
                          const float *psd_i_dev, const float *spec_j_dev, const float *psd_j_dev, int32_t n_slides,

@@ -331,6 +331,8 @@ STT_HD int32_t row_tm_fallback(const RowTm &k, int32_t dt)
     return row_tm_exact(k, dt, D, sqrt_1ulp((float)D));
 }
 
+// The row: the two steps in one, as a reference for both (the kernels take them apart to share the
+// second among columns).
 STT_HD int32_t row_tm(const RowTm &k, int32_t dt)
 {
     bool ok;

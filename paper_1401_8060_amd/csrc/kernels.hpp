@@ -1204,6 +1204,8 @@ __device__ __forceinline__ uint64_t score_block(const MapP &m, const GenP &g, co
         walk_slab<SC, TPT, HW, E, kWalkMask>(c0, next_slab(c0), col_bytes, s);
         flush(c0);
     }
+    // seeds lie between slabs: on slabs wider than the period (16 columns from 1021 columns of extent on, 8
+    // from 1440) the core takes exact rows, at the speed of the code before the lazy ones
     if (seed_cols >= SC) {
         int seeded = c0;  // the column of num
         auto seed = [&](int c) {
@@ -1363,7 +1365,9 @@ __device__ __forceinline__ uint64_t score_block_regs(const MapP &m, const GenP &
 // every wave serialise across the chip); k_reduce_keys folds the slots.
 // Four templates per lane: at least 4 waves per SIMD (at most 128 VGPRs), so that two workgroups
 // of 512 lanes, or four of 256, can share a CU when their slabs fit its LDS. Two per lane with DMA
-// staging: 8 waves (64 VGPRs, two workgroups of 1024 lanes).
+// staging: 8 waves (64 VGPRs, two workgroups of 1024 lanes). These bounds are kept by spilling state that
+// the lazy and the masked loops do not touch: 10 VGPRs for 1024 x 2 on SC = 4, 31 for its batch, whose exact
+// core (kWalkExact) loads and stores two words per slab.
 template <int TPT, int SC> constexpr int kSlabWavesPerSimd = TPT <= 2 && SC > 0 ? 8 : 4;
 
 template <int WG, int TPT, bool HW, int MAPT, int SC>
@@ -1428,7 +1432,10 @@ __global__ __launch_bounds__(256) void k_make_tracks_tm(GenP g, uint64_t first, 
     if (i < n) out[i] = draw_track_tm(g, first + (uint64_t)i);
 }
 
-// A wave per template, lanes over flush groups (as k_score_wave, with an independent row per column).
+// A wave per template, lanes over flush groups (as k_score_wave, with an independent row per column): the
+// FP32 pass over the whole group, then one copy of the exact path for the columns that it leaves open, each
+// lane its own next one, then the gathers. Compiled in at each of the 16 columns the exact path was half of
+// the code (5600 instructions, now 3400): lists of 16 to 50 000 templates take 10 % less on average.
 template <bool EXPL, bool HW, int MAPT>
 __global__ __launch_bounds__(256) void k_score_tm(MapP m, GenP g, const TrkTm *tr, uint64_t first, int64_t n,
                                                   int32_t norm, float *snr, uint64_t *best)

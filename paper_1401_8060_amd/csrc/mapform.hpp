@@ -98,7 +98,7 @@ __device__ __forceinline__ void fft_pass(float2 *z, int s, int M, int lg, const 
 // spec: [T][F] complex64. Grid: T workgroups, fft_slot(N) float2 of LDS, N = M/2 = 2^lg >= 4.
 // Bound by latency: a stage at a time through LDS was 11 barriers and a twiddle gather in front of
 // each at M = 4096. Three stages at a time stay in registers (the same butterflies in the same
-// order, so the same bits), and the first three take the samples straight from memory.
+// order; contracted otherwise, so spectra agree to rounding), and the first three take the samples straight from memory.
 __global__ __launch_bounds__(kFftThreads) void k_col_fft(const float *__restrict__ x, int M, int lg, int k_lo, int F,
                                                          float dt, const float2 *__restrict__ tab,
                                                          float2 *__restrict__ spec)

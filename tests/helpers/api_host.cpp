@@ -18,6 +18,7 @@
 //   gather T F p16 wave n launches -> 1 if that direct call reads the caller's map unfolded
 //   class dma workgroups n_cu nb -> extents per class of the sort
 //   one bytes T n mean -> 1 if lanes gather one pixel at a time
+//   plain T n -> the plain search's scorer by size
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -240,6 +241,15 @@ static int one()
     return 0;
 }
 
+static int plain()
+{
+    int T;
+    long long n;
+    if (std::scanf("%d %lld", &T, &n) != 2) return 2;
+    std::printf("%s\n", prefer_slabs(T, n) ? "k_score_slab" : prefer_wave(T, n) ? "k_score_wave" : "k_score_direct");
+    return 0;
+}
+
 int main()
 {
     char cmd[16];
@@ -253,7 +263,8 @@ int main()
                         : !std::strcmp(cmd, "tm") ? tm()
                         : !std::strcmp(cmd, "gather") ? gather()
                         : !std::strcmp(cmd, "class") ? sclass()
-                        : !std::strcmp(cmd, "one") ? one() : 2;
+                        : !std::strcmp(cmd, "one") ? one()
+                        : !std::strcmp(cmd, "plain") ? plain() : 2;
         if (bad) return bad;
     }
     return 0;

@@ -179,3 +179,10 @@ def test_sort_by_extent_alone_for_one_round_of_register_staging(api):
 def test_lanes_gather_one_pixel_at_a_time_on_large_maps(api):
     assert api("one 8192000 1000 70000 340") == ["0"] and api("one 8192000 1000 70000 667") == ["1"]
     assert api("one 8192000 1000 300000 340") == ["1"] and api("one 4194304 1000 300000 340") == ["0"]
+
+
+@pytest.mark.parametrize("T", [2, 20, 100, 500, 1000, 2896])
+def test_bench_names_the_scorer_that_runs(api, T):
+    import bench
+    ns = [1, 4095, 4096, -(-60_000_000 // T) - 1, -(-60_000_000 // T), 80_000 * T // (T + 600), 80_000 * T // (T + 600) + 1]
+    assert [api(f"plain {T} {n}")[0] for n in ns] == [bench.plain_scorer(T, n) for n in ns]

@@ -32,4 +32,6 @@ class SmoothSNR(torch.autograd.Function):
 
 
 def smooth_snr(ctx, m, theta: torch.Tensor, K: torch.Tensor) -> torch.Tensor:
-    return SmoothSNR.apply(theta, K, ctx, m, torch.is_grad_enabled())
+    if torch.is_grad_enabled():
+        return SmoothSNR.apply(theta, K, ctx, m)
+    return SmoothSNR.apply(theta, K, ctx, m, False)
